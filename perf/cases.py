@@ -32,6 +32,7 @@ NETS = {
     "repvgg": (4, (32, 64, 96, 128), (3, 5, 7, 9, 11), "softplus", 5),
 }
 EPS_NORM, EPS_ALBEDO, GAMMA, NEAR, FAR, EPS_SMAPE = 1e-10, 1e-3, 2.2, 1.0, 10.0, 0.01
+STEP, LR, BETA1, BETA2, ADAM_EPS = 100, 1e-3, 0.9, 0.999, 1e-8
 
 
 def listed():
@@ -52,7 +53,7 @@ def listed():
         # one serving batch: a frame of each served resolution in one call
         {"name": "batch_hd_bf16_serving", "kind": "batch", "net": "hd", "prec": "bf16",
          "sizes": "360x640,720x1280,1080x1920,1440x2560"},
-        # the network's training step up to the gradients: 8 crops, fp32
+        # one training step of the network in the middle of a run (its Adam moments are in hand): 8 crops, fp32
         {"name": "train_hd_8x256", "kind": "train", "net": "hd", "prec": "fp32", "sizes": ",".join(["256x256"] * 8)},
         # decode and its adjoint alone, under autograd (a caller's own network in front)
         {"name": "decode_grad_8x256", "kind": "decode_grad", "n": 8, "h": 256, "w": 256, "kernels": "3,5,7,9,11"},
@@ -91,9 +92,9 @@ def draw(rng):
         sizes = [_size(rng, 1.6e4, top / n if prec == "fp32" else top, align) for _ in range(n)]
         return {"kind": kind, "net": net, "prec": prec, "sizes": ",".join("%dx%d" % s for s in sizes)}
     if kind == "train":
-        n = rng.randint(1, 8)
-        one = _size(rng, 4e3, 6.5e4, 8)
-        sizes = [one] * n if rng.random() < 0.7 else [_size(rng, 4e3, 2.6e4, 8) for _ in range(n)]
+        n = rng.randint(3, 8)
+        one = _size(rng, 2e4, 6.5e4, 8)
+        sizes = [one] * n if rng.random() < 0.7 else [_size(rng, 2e4, 3.3e4, 8) for _ in range(n)]
         return {"kind": "train", "net": "hd", "prec": "fp32", "sizes": ",".join("%dx%d" % s for s in sizes)}
     if kind == "decode_grad":
         n = rng.randint(1, 8)
@@ -196,6 +197,13 @@ def _weights(net, seed):
     return np.concatenate(parts)
 
 
+def _moments(net, seed):
+    """Adam's moments some steps into a run (gradients of the default initialisation are 1e-4 to 6e-4 a value)."""
+    n, g = _weights(net, seed).size, _gen(seed + 31)
+    m = 3e-4 * torch.randn(n, device=DEV, generator=g)
+    return m, (3e-4) ** 2 * (0.5 + torch.rand(n, device=DEV, generator=g))
+
+
 def _config(net):
     levels, ch, kernels, act, k = NETS[net]
     return synth.NetConfig(levels=levels, channels=ch, kernel_sizes=kernels, weight_act=act, conv_size=k,
@@ -280,7 +288,8 @@ def prepare(case, seed):
         if kind == "train":
             st["targets"] = [f["clean"] for f in frames]
             st["ws"] = torch.empty(wskp.wskp_train_workspace_size(dn.h, hs, ws), dtype=torch.uint8, device=DEV)
-            st["grad"] = torch.empty(blob.size, dtype=torch.float32, device=DEV)
+            st["m"], st["v"] = _moments(case["net"], seed)
+            st["grad"], st["weights"] = torch.empty_like(st["m"]), torch.empty_like(st["m"])
             st["loss"] = torch.empty(1, dtype=torch.float32, device=DEV)
         else:
             dn.workspace(list(hs), list(ws))
@@ -314,7 +323,12 @@ def run(state):
         return [f["out"] for f in state["frames"]]
     if kind == "train":
         wskp.wskp_train_grads(dn.h, state["frames"], state["targets"], state["grad"], state["loss"], state["ws"], EPS_SMAPE)
-        return {"grad": state["grad"], "loss": state["loss"], "out": [f["out"] for f in state["frames"]]}
+        # the weights, not the gradient, come back: a change of rounding anywhere in the forward pass carries a few
+        # pre-activations across the ReLU's zero, which moves the raw gradient by up to 6e-5 of its norm
+        wskp.wskp_adam(dn.h, state["grad"], state["m"], state["v"], STEP, LR, BETA1, BETA2, ADAM_EPS)
+        wskp.wskp_get_weights(dn.h, state["weights"])
+        return {"weights": state["weights"], "m": state["m"], "v": state["v"], "loss": state["loss"],
+                "out": [f["out"] for f in state["frames"]]}
     if kind == "decode":
         wskp.wskp_decode(dn.h, state["head"], state["c"], state["mod"], state["out"])
         return state["out"]
@@ -342,9 +356,9 @@ def work(case):
         dec = 30.0 * len(kernels) * px
         if kind == "train":
             # forward, weight gradients, and input gradients of all but the first conv; reads the frames and
-            # the targets, writes the outputs and the gradients
+            # the targets, writes the outputs; reads and writes the weights and the moments
             first = 2.0 * k * k * dims[0][0] * dims[0][1] * px
-            return {"bytes": px * (40 + 12 + 12) + 2 * wbytes, "flops": 3 * conv - first + 3 * dec}
+            return {"bytes": px * (40 + 12 + 12) + 6 * wbytes, "flops": 3 * conv - first + 3 * dec}
         return {"bytes": px * (40 + 12) + wbytes * {"fp32": 1, "bf16": 0.5, "fp8": 0.25}[case["prec"]], "flops": conv + dec}
     if kind in ("decode", "decode_grad"):
         px, m = case["n"] * case["h"] * case["w"], len(_kernels(case))
@@ -457,7 +471,12 @@ def exact(case, seed):
                 acc += g
             outs.append(y.detach())
             loss = loss + part.detach()
-        return {"grad": torch.cat([g.reshape(-1) for g in grads]), "loss": loss.reshape(1), "out": outs}
+        grad, w = torch.cat([g.reshape(-1) for g in grads]), torch.cat([p.detach().reshape(-1) for p in flat])
+        m, v = (t.double() for t in _moments(case["net"], seed))
+        m = BETA1 * m + (1 - BETA1) * grad
+        v = BETA2 * v + (1 - BETA2) * grad * grad
+        w = w - LR * (m / (1 - BETA1 ** STEP)) / ((v / (1 - BETA2 ** STEP)).sqrt() + ADAM_EPS)
+        return {"weights": w, "m": m, "v": v, "loss": loss.reshape(1), "out": outs}
     if kind in ("decode", "decode_grad"):
         ks = _kernels(case)
         head, c, mod, g = (t.double() for t in _decode_inputs(case, seed))

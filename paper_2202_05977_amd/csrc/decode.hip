@@ -70,10 +70,10 @@ __device__ __forceinline__ bool decode_locate_at(const DecodeCfg &dc, const Fram
     auto tiles = [](int H, int W) { return ((W + kDTX - 1) / kDTX) * ((H + kDTY - 1) / kDTY); };
     int t = xcd_logical_id(u, nbk);
     if constexpr (FRAMES) {
-        int n;
-        t = batch_tile_id(fa, u, nbk, n);
+        int first, n;
+        t = batch_tile_id(fa, u, nbk, first, n);
         if (t < 0) return false;
-        const int f = batch_frame(fa, n, t, tiles);
+        const int f = batch_frame(fa, first, n, t, tiles);
         if (f < 0) return false;
         const FrameDesc &fd = frame_at(fa, f);
         io.H = fd.H;
@@ -600,10 +600,10 @@ __global__ __launch_bounds__(kFThreads, 4) void decode_tile_kernel(DecodeCfg dc,
     int x0, y0;
     {
         auto tiles = [&](int H, int W) { return ((W + TW - 1) / TW) * ((H + TH - 1) / TH); };
-        int n;
-        int t = batch_tile_id(fa, blockIdx.x, gridDim.x, n);
+        int first, n;
+        int t = batch_tile_id(fa, blockIdx.x, gridDim.x, first, n);
         if (t < 0) return;
-        const int f = batch_frame(fa, n, t, tiles);   // t becomes the tile within frame f
+        const int f = batch_frame(fa, first, n, t, tiles);   // t becomes the tile within frame f
         if (f < 0) return;
         const FrameDesc &fd = frame_at(fa, f);
         io.H = fd.H;

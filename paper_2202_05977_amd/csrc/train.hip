@@ -21,10 +21,10 @@
 // Gradient kernels (NHWC fp32, zero padding, conv = 3x3 cross-correlation):
 //   dgrad  gin[p][ci] = sum_{tap,co} gm[p - off(tap)][co] w[co][ci][tap]:
 //          itself a 3x3 conv of gm with the kernel flipped and its channel
-//          axes swapped, run by the fp32 forward conv kernel (MFMA,
-//          conv3x3.hip) on weights that tr_pack_dgrad lays out for it; the
-//          head's 2M output channels are padded with zeros to a multiple
-//          of 16 (its gradient dh is written with that row stride)
+//          axes swapped, run by the split conv kernel (conv_split.hip) on
+//          weights that conv_split_pack lays out for it; the head's 2M
+//          output channels are padded with zeros to a multiple of 16 (its
+//          gradient dh is written with that row stride)
 //   wgrad  dw[co][ci][tap] = sum_p gm[p][co] in[p + off(tap)][ci],
 //          db[co] = sum_p gm[p][co]: a GEMM over pixels,
 //          tr_wgrad_mfma_kernel (v_mfma_f32_16x16x4f32, 4 pixels per step;
@@ -565,25 +565,6 @@ hipError_t tr_mask(long n, int nf, const float *g, const float *act, long sa, fl
     TR_LAUNCH(tr_mask_kernel, n * nf, n, nf, g, act, sa, gm);
     return hipGetLastError();
 }
-__global__ __launch_bounds__(kTrThreads) void tr_pack_dgrad_kernel(int Ci, int Co, int Co_pad, int Cout_pad,
-                                                                    const float *w, float *packed)
-{
-    const long n = (long)Co_pad * 9 * Cout_pad;
-    const long i = (long)blockIdx.x * kTrThreads + threadIdx.x;
-    if (i >= n) return;
-    const int ci = (int)(i % Cout_pad);
-    const long ct = i / Cout_pad;            // (chunk * 9 + tap) * 16 + c
-    const int c16 = (int)(ct % 16), ctap = (int)(ct / 16);
-    const int t = ctap % 9, co = (ctap / 9) * 16 + c16;
-    gstore(packed + i, ci < Ci && co < Co ? gload(w + ((long)co * Ci + ci) * 9 + (8 - t)) : 0.f);
-}
-
-hipError_t tr_pack_dgrad(int Ci, int Co, int Co_pad, int Cout_pad, const float *w, float *packed, hipStream_t s)
-{
-    TR_LAUNCH(tr_pack_dgrad_kernel, (long)Co_pad * 9 * Cout_pad, Ci, Co, Co_pad, Cout_pad, w, packed);
-    return hipGetLastError();
-}
-
 static int wgrad_blocks(int Ci, int Co)
 {
     const int cib = (Ci + 15) / 16, cob = (Co + 15) / 16;
@@ -679,6 +660,7 @@ hipError_t tr_adam(long n, float *w, const float *g, float *m, float *v, float l
     TR_LAUNCH(tr_adam_kernel, n, n, w, g, m, v, lr, b1, b2, c1, c2, eps);
     return hipGetLastError();
 }
+
 hipError_t tr_repack(int Cin, int Cout, int CK, int nch, int Cout_pad, const float *blob, float *packed, float *bias,
                      hipStream_t s)
 {

@@ -104,7 +104,11 @@ struct wskp_ctx {
     int act_bytes = 4;
     bool pooled = false;   // encoder epilogues write 2x2 means p_l; enc_{l+1} reads them plainly
     std::vector<LayerPlan> layers;
+    // fp32 3x3 nets: the same layers on the split kernel (conv_split.hip), for
+    // frames of at least kSplitPixels
+    std::vector<LayerPlan> split;
     void *dweights = nullptr;
+    void *dsplit = nullptr;       // packed weights of `split` (offsets w_off)
     float *dmaster = nullptr;     // fp32 handles: the weight blob (OIHW + bias, blob order), for training
     std::vector<size_t> blob_off; // offset of each conv's weights in the blob
     DecodeCfg dc{};
@@ -120,6 +124,7 @@ struct wskp_ctx {
         hipStream_t s;
         bool reverse;
         std::vector<int> caps;   // workgroups of each launch
+        std::vector<int> rows;   // tile rows of each conv launch, negative on the split kernel
         hipGraphExec_t exec;
         char *tab;               // device: header + descriptors
     };
@@ -143,12 +148,27 @@ static constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
 static void *g_scratch_ptr[kMaxDevices];
 
+// FP32 3x3 convs: frames of at least this many pixels run the split kernel, in
+// denoising and in training alike (a frame's result depends neither on its
+// batch nor on who asks).  The split kernel is faster on small frames too
+// (128 x 128, three levels: 68 us against 80); they keep
+// v_mfma_f32_16x16x4f32 for the sake of training, whose crops are of 256 x 256
+// and less: a gradient is taken through the forward pass's ReLU masks, and any
+// change of the forward rounding carries a few pre-activations within it of
+// zero to the other side, which moves the gradient of a batch of such crops by
+// 2e-6 to 6e-5 of its norm.  720p is 7 times above the line.
+static constexpr long kSplitPixels = 1L << 17;
+
 static constexpr int kRingSlots = 8;
 static constexpr int kMaxBatch = 1024;
-static constexpr size_t kTableHeader = 256;   // frame count, tile count of each launch; padded
+// header of a frame table: three blocks of first frame, frame count and the
+// tile count of each launch (convs of the first and of the second group,
+// decode), padded
+static constexpr size_t kHeaderInts = 64;
+static constexpr size_t kTableHeader = 3 * kHeaderInts * sizeof(int);
 static constexpr size_t kSlotBytes = kTableHeader + sizeof(FrameDesc) * kMaxBatch;
 static constexpr size_t kMaxGraphs = 256;
-static_assert(kTableHeader >= sizeof(int) * (2 + 2 * WSKP_MAX_LEVELS), "header holds n and every launch's tiles");
+static_assert(kHeaderInts >= 3 + 2 * WSKP_MAX_LEVELS, "a block holds first, n and every launch's tiles");
 
 // ---------------------------------------------------------------------------
 static wskp_status_t check_config(const wskp_config_t *c)
@@ -303,6 +323,18 @@ extern "C" wskp_status_t wskp_repvgg_merge(int cin, int cout, const float *w1, c
     if (identity)
         for (int c = 0; c < cout; ++c) w_out[(((size_t)c * cin + c) * 5 + 2) * 5 + 2] += 1.f;
     return WSKP_OK;
+}
+
+// Writes the split kernel's weights from the handle's weight blob.
+static hipError_t pack_split(const wskp_ctx *h, hipStream_t s)
+{
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; k < h->split.size() && e == hipSuccess; ++k) {
+        const LayerPlan &lp = h->split[k];
+        e = conv_split_pack(lp.Cin, lp.L.Cout, false, h->dmaster + h->blob_off[k],
+                            static_cast<char *>(h->dsplit) + lp.w_off, s);
+    }
+    return e;
 }
 
 extern "C" wskp_status_t wskp_create(const wskp_config_t *cfg, const float *host_weights,
@@ -474,6 +506,27 @@ extern "C" wskp_status_t wskp_create(const wskp_config_t *cfg, const float *host
                                   : nullptr;
     }
 
+    if (h->prec == WSKP_PREC_FP32 && ks == 3) {
+        h->split = h->layers;
+        size_t bytes = 0;
+        for (auto &lp : h->split) {
+            conv_split_layer(lp.L, lp.Cin);
+            lp.w_off = bytes;
+            bytes += align_up(conv_split_weight_bytes(lp.Cin, lp.L.Cout));
+        }
+        e = hipMalloc(&h->dsplit, bytes);
+        for (auto &lp : h->split) lp.L.w = static_cast<char *>(h->dsplit) + lp.w_off;
+        if (e == hipSuccess) e = pack_split(h, nullptr);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        if (e != hipSuccess) {
+            if (h->dsplit) (void)hipFree(h->dsplit);
+            (void)hipFree(h->dmaster);
+            (void)hipFree(h->dweights);
+            delete h;
+            return hip_fail(e, "split weights", e == hipErrorOutOfMemory ? WSKP_E_OOM : WSKP_E_DEVICE);
+        }
+    }
+
     // ---- decode configuration
     h->dc.M = M;
     h->dc.R = 0;
@@ -506,6 +559,7 @@ extern "C" wskp_status_t wskp_destroy(wskp_handle_t h)
     if (h->ring) (void)hipHostFree(h->ring);
     if (h->dweights) (void)hipFree(h->dweights);
     if (h->dmaster) (void)hipFree(h->dmaster);
+    if (h->dsplit) (void)hipFree(h->dsplit);
     delete h;
     return WSKP_OK;
 }
@@ -641,7 +695,57 @@ static wskp_status_t set_device(const wskp_ctx *h)
 
 static int n_launches(const wskp_ctx *h) { return (int)h->layers.size() + 1; }
 
+// One conv launch of a batch: the layer with the tiling chosen for the
+// batch's sizes, and its workgroup count.
+struct ConvLaunch {
+    ConvLayer L;
+    int mode, epi;
+    bool split;
+    int blocks;
+};
+
+// Frames first .. first + n - 1 of a batch, whose convs run together.
+struct ConvGroup {
+    int first, n;
+    std::vector<ConvLaunch> convs;
+};
+
+static bool uses_split(const wskp_ctx *h, int H, int W) { return !h->split.empty() && (long)H * W >= kSplitPixels; }
+
+// The conv launches for n frames, those that run the split kernel last: one
+// group, or two where both kinds are there.
+static std::vector<ConvGroup> plan_convs(const wskp_ctx *h, int n, const int *Hs, const int *Ws)
+{
+    std::vector<ConvGroup> groups;
+    for (int f = 0; f < n;) {
+        const bool split = uses_split(h, Hs[f], Ws[f]);
+        int e = f + 1;
+        while (e < n && uses_split(h, Hs[e], Ws[e]) == split) ++e;
+        ConvGroup g{f, e - f, {}};
+        for (const LayerPlan &lp : split ? h->split : h->layers) {
+            ConvLaunch c{lp.L, lp.mode, lp.epi, split, 0};
+            c.blocks = conv_grid(c.L, g.n, Hs + f, Ws + f);
+            // 4-row tiles where 8-row ones leave CUs without their two workgroups
+            if (split && c.blocks < 512) {
+                c.L.th = 4;
+                c.blocks = conv_grid(c.L, g.n, Hs + f, Ws + f);
+            }
+            g.convs.push_back(c);
+        }
+        groups.push_back(std::move(g));
+        f = e;
+    }
+    return groups;
+}
+
+static hipError_t launch_planned(const wskp_ctx *h, const ConvLaunch &c, const FrameArg &fa, int blocks, hipStream_t s)
+{
+    return c.split ? launch_conv_split(c.L, c.mode, c.epi, fa, blocks, s)
+                   : launch_conv(c.L, c.mode, c.epi, h->prec, fa, blocks, s);
+}
+
 // Queues the whole network and the decode for the frames of `fa`.
+// (of two kinds of convs: those of the split kernel last).
 static wskp_status_t run_frames(wskp_ctx *h, const FrameArg &fa, int n, const int *Hs, const int *Ws,
                                 hipStream_t s)
 {
@@ -650,10 +754,15 @@ static wskp_status_t run_frames(wskp_ctx *h, const FrameArg &fa, int n, const in
         ev = h->tev.data() + (size_t)h->t_calls++ * (n_launches(h) + 1);
     int k = 0;
     if (ev) (void)hipEventRecord(ev[k], s);
-    for (const LayerPlan &lp : h->layers) {
-        const int blocks = conv_grid(lp.L, n, Hs, Ws);
-        hipError_t e = launch_conv(lp.L, lp.mode, lp.epi, h->prec, fa, blocks, s);
-        if (e != hipSuccess) return hip_fail(e, "conv launch", WSKP_E_LAUNCH);
+    const std::vector<ConvGroup> groups = plan_convs(h, n, Hs, Ws);
+    for (size_t i = 0; i < h->layers.size(); ++i) {
+        for (const ConvGroup &g : groups) {
+            FrameArg ga = fa;
+            ga.first = g.first;
+            ga.n = g.n;
+            hipError_t e = launch_planned(h, g.convs[i], ga, g.convs[i].blocks, s);
+            if (e != hipSuccess) return hip_fail(e, "conv launch", WSKP_E_LAUNCH);
+        }
         if (ev) (void)hipEventRecord(ev[++k], s);
     }
     hipError_t e = launch_decode_frames(h->dc, fa, decode_grid(h->dc, n, Hs, Ws), s);
@@ -784,7 +893,7 @@ static int next_pow2(int v)
 // executable graph whose launches read the frame count and the descriptors
 // from the device buffer c.tab (header, then descriptors), on the handle's
 // own capture stream.
-static wskp_status_t capture_batch_graph(wskp_ctx *h, wskp_ctx::BatchGraph &c)
+static wskp_status_t capture_batch_graph(wskp_ctx *h, wskp_ctx::BatchGraph &c, const std::vector<ConvGroup> &groups)
 {
     hipError_t e;
     if (!h->cap_stream && (e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking)) != hipSuccess)
@@ -795,19 +904,23 @@ static wskp_status_t capture_batch_graph(wskp_ctx *h, wskp_ctx::BatchGraph &c)
     fa.table = reinterpret_cast<const FrameDesc *>(c.tab + kTableHeader);
     fa.n = 0;
     fa.reverse = c.reverse ? 1 : 0;
-    fa.dev_n = reinterpret_cast<const int *>(c.tab);
+    const int *hdr = reinterpret_cast<const int *>(c.tab);
     hipStream_t cs = h->cap_stream;
     if ((e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed)) != hipSuccess) {
         (void)hipFree(c.tab);
         return hip_fail(e, "hipStreamBeginCapture");
     }
     hipError_t le = hipSuccess;
-    for (size_t i = 0; i < h->layers.size() && le == hipSuccess; ++i) {
-        const LayerPlan &lp = h->layers[i];
-        fa.launch = (int)i;
-        le = launch_conv(lp.L, lp.mode, lp.epi, h->prec, fa, c.caps[i], cs);
+    size_t k = 0;
+    for (size_t gi = 0; gi < groups.size(); ++gi) {
+        fa.dev_n = hdr + gi * kHeaderInts;
+        for (size_t i = 0; i < groups[gi].convs.size() && le == hipSuccess; ++i) {
+            fa.launch = (int)i;
+            le = launch_planned(h, groups[gi].convs[i], fa, c.caps[k++], cs);
+        }
     }
-    fa.launch = (int)h->layers.size();
+    fa.dev_n = hdr + 2 * kHeaderInts;
+    fa.launch = 0;
     if (le == hipSuccess) le = launch_decode_frames(h->dc, fa, c.caps.back(), cs);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(cs, &graph);
@@ -865,17 +978,29 @@ extern "C" wskp_status_t wskp_denoise_batch(wskp_handle_t h, void *stream, int n
     // graph replay: the executable graph of this stream and capacity bucket
     // (launch grids rounded up to powers of two), captured on first use
     wskp_ctx::BatchGraph *g = nullptr;
-    std::vector<int> tiles;
+    // frames in table order: those of the split kernel last
+    std::vector<int> order(n), Ht(n), Wt(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_partition(order.begin(), order.end(), [&](int i) { return !uses_split(h, Hs[i], Ws[i]); });
+    for (int i = 0; i < n; ++i) {
+        Ht[i] = Hs[order[i]];
+        Wt[i] = Ws[order[i]];
+    }
+    std::vector<ConvGroup> groups;
     if (flags & WSKP_BATCH_GRAPH) {
-        std::vector<int> caps;
-        for (const LayerPlan &lp : h->layers) tiles.push_back(conv_grid(lp.L, n, Hs.data(), Ws.data()));
-        tiles.push_back(decode_grid(h->dc, n, Hs.data(), Ws.data()));
-        for (int t : tiles) caps.push_back(next_pow2(t));
+        groups = plan_convs(h, n, Ht.data(), Wt.data());
+        std::vector<int> caps, rows;
+        for (const ConvGroup &cg : groups)
+            for (const ConvLaunch &c : cg.convs) {
+                caps.push_back(next_pow2(c.blocks));
+                rows.push_back(c.split ? -c.L.th : c.L.th);
+            }
+        caps.push_back(next_pow2(decode_grid(h->dc, n, Ht.data(), Wt.data())));
         for (auto &c : h->graphs)
-            if (c.s == s && c.reverse == reverse && c.caps == caps) g = &c;
+            if (c.s == s && c.reverse == reverse && c.caps == caps && c.rows == rows) g = &c;
         if (!g && h->graphs.size() < kMaxGraphs) {
-            wskp_ctx::BatchGraph c{s, reverse, caps, nullptr, nullptr};
-            if ((st = capture_batch_graph(h, c)) != WSKP_OK) return st;
+            wskp_ctx::BatchGraph c{s, reverse, caps, rows, nullptr, nullptr};
+            if ((st = capture_batch_graph(h, c, groups)) != WSKP_OK) return st;
             h->graphs.push_back(c);
             g = &h->graphs.back();
         }
@@ -888,13 +1013,23 @@ extern "C" wskp_status_t wskp_denoise_batch(wskp_handle_t h, void *stream, int n
     char *sbase = h->ring + kSlotBytes * slot;
     FrameDesc *tab = reinterpret_cast<FrameDesc *>(sbase + kTableHeader);
     int *hdr = reinterpret_cast<int *>(sbase);
-    hdr[0] = n;
-    for (size_t i = 0; i < tiles.size(); ++i) hdr[1 + i] = tiles[i];
-    char *base = static_cast<char *>(ws) + table_bytes(n);
-    for (int i = 0; i < n; ++i) {
-        fill_frame(h, tab[i], base, frames[i]);
-        base += frame_bytes(h, Hs[i], Ws[i], nullptr, nullptr, nullptr);
+    for (size_t gi = 0; gi < groups.size(); ++gi) {
+        int *b = hdr + gi * kHeaderInts;
+        b[0] = groups[gi].first;
+        b[1] = groups[gi].n;
+        for (size_t i = 0; i < groups[gi].convs.size(); ++i) b[2 + i] = groups[gi].convs[i].blocks;
     }
+    hdr[2 * kHeaderInts] = 0;
+    hdr[2 * kHeaderInts + 1] = n;
+    hdr[2 * kHeaderInts + 2] = decode_grid(h->dc, n, Ht.data(), Wt.data());
+    // (workspace regions in the caller's order)
+    std::vector<char *> base(n);
+    char *at = static_cast<char *>(ws) + table_bytes(n);
+    for (int i = 0; i < n; ++i) {
+        base[i] = at;
+        at += frame_bytes(h, Hs[i], Ws[i], nullptr, nullptr, nullptr);
+    }
+    for (int i = 0; i < n; ++i) fill_frame(h, tab[i], base[order[i]], frames[order[i]]);
     if (g) {
         if ((e = hipMemcpyAsync(g->tab, sbase, kTableHeader + sizeof(FrameDesc) * n, hipMemcpyHostToDevice,
                                 s)) != hipSuccess)
@@ -911,7 +1046,7 @@ extern "C" wskp_status_t wskp_denoise_batch(wskp_handle_t h, void *stream, int n
     fa.n = n;
     fa.reverse = reverse ? 1 : 0;
     fa.dev_n = nullptr;
-    return run_frames(h, fa, n, Hs.data(), Ws.data(), s);
+    return run_frames(h, fa, n, Ht.data(), Wt.data(), s);
 }
 
 extern "C" wskp_status_t wskp_decode(wskp_handle_t h, void *stream, int N, int H, int W,
@@ -1010,11 +1145,11 @@ static size_t train_plan(const wskp_ctx *h, int Hm, int Wm, int nf, char *base, 
     // in, C_in out: encoders >= 1, decoders, the head) and the zero bias
     // come first, at offsets that do not depend on the frame size: they are
     // written once per call and serve every frame
-    auto r16 = [](int c) { return (size_t)(c + 15) / 16 * 16; };
+    auto wf = [](int ci, int co) { return conv_split_weight_bytes(ci, co) / sizeof(float); };
     TrainScratch t{};
-    for (int l = 1; l < L; ++l) t.wpk[l] = take((size_t)ch[l] * 9 * r16(ch[l - 1]));
-    for (int l = 0; l + 1 < L; ++l) t.wpk[L + (L - 2 - l)] = take((size_t)ch[l] * 9 * r16(ch[l + 1] + ch[l]));
-    t.wpk[2 * L - 1] = take((size_t)ldh * 9 * r16(ch[0]));
+    for (int l = 1; l < L; ++l) t.wpk[l] = take(wf(ch[l], ch[l - 1]));
+    for (int l = 0; l + 1 < L; ++l) t.wpk[L + (L - 2 - l)] = take(wf(ch[l], ch[l + 1] + ch[l]));
+    t.wpk[2 * L - 1] = take(wf(2 * M, ch[0]));
     t.zb = take(256);
     t.X = take(F * 10 * P);
     t.head = take(F * 2 * M * P);
@@ -1119,10 +1254,10 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
     auto bofs = [&](size_t k, int Ci, int Co) { return grad + h->blob_off[k] + (size_t)Ci * Co * 9; };
     hipError_t e = tr_fill((long)nw, 0.f, grad, s);
     // input gradient of conv k (Ci -> Co forward): gin = conv(gm, w flipped,
-    // in and out channels swapped), on the matrix cores with the fp32
-    // forward kernel on the weights packed for it; gm has ldg >= Co channels
-    // (the head's 2M padded with zeros to a multiple of 16, the kernel's
-    // channel chunk; Ci, a network width, is one already)
+    // in and out channels swapped), on the split kernel with the weights
+    // packed for it; gm has ldg >= Co channels (the head's 2M padded with
+    // zeros to a multiple of 16, the kernel's channel chunk; Ci, a network
+    // width, is one already)
     // gradients of nf frames, frame f's at gm + f sg, into gin + f si
     auto dgrad = [&](const TrainScratch &t, size_t k, int Hl, int Wl, int Ci, int ldg, int nf, const float *gm,
                      long sg, float *gin, long si) -> hipError_t {
@@ -1134,14 +1269,8 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
         c.C0 = ldg;
         c.C1 = 0;
         c.ks = 3;
-        c.CK = 16;
-        c.Cin_pad = ldg;
         c.Cout = Ci;
-        const int nblk = Ci / 16;
-        c.NB = nblk % 4 == 0 ? 4 : (nblk % 2 == 0 ? 2 : 1);
-        c.groups = nblk / c.NB;
-        c.Cout_pad = nblk * 16;
-        c.th = conv_tile_rows(WSKP_PREC_FP32, CONV_PLAIN, 16, 0, false, 3);
+        conv_split_layer(c, ldg);
         c.pool_idx = -1;
         c.out_kind = 0;
         c.out_idx = 1;
@@ -1162,19 +1291,24 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
             fa.table = t.tab;
         }
         const std::vector<int> hv(nf, Hl), wv(nf, Wl);
-        return launch_conv(c, CONV_PLAIN, EPI_LINEAR, WSKP_PREC_FP32, fa, conv_grid(c, nf, hv.data(), wv.data()), s);
+        int blocks = conv_grid(c, nf, hv.data(), wv.data());
+        if (blocks < 512) {   // as in plan_convs
+            c.th = 4;
+            blocks = conv_grid(c, nf, hv.data(), wv.data());
+        }
+        return launch_conv_split(c, CONV_PLAIN, EPI_LINEAR, fa, blocks, s);
     };
     {
         TrainScratch t;
         train_plan(h, Hs[0], Ws[0], 1, static_cast<char *>(ws) + align_up(fwd), &t);
         if (e == hipSuccess) e = tr_fill(256, 0.f, t.zb, s);
-        if (e == hipSuccess) e = tr_pack_dgrad(ch[0], 2 * M, ldh, ch[0], wofs(head_k), t.wpk[head_k], s);
+        if (e == hipSuccess) e = conv_split_pack(2 * M, ch[0], true, wofs(head_k), t.wpk[head_k], s);
         for (int l = 0; l + 1 < L && e == hipSuccess; ++l) {
             const size_t k = (size_t)L + (L - 2 - l);
-            e = tr_pack_dgrad(ch[l + 1] + ch[l], ch[l], ch[l], ch[l + 1] + ch[l], wofs(k), t.wpk[k], s);
+            e = conv_split_pack(ch[l], ch[l + 1] + ch[l], true, wofs(k), t.wpk[k], s);
         }
         for (int l = 1; l < L && e == hipSuccess; ++l)
-            e = tr_pack_dgrad(ch[l - 1], ch[l], ch[l], ch[l - 1], wofs(l), t.wpk[l], s);
+            e = conv_split_pack(ch[l], ch[l - 1], true, wofs(l), t.wpk[l], s);
     }
     // Frames of one size run the backward pass as one group, every kernel
     // over all of them (frame k's tensors at a constant stride: fs floats
@@ -1292,7 +1426,7 @@ extern "C" wskp_status_t wskp_adam(wskp_handle_t h, void *stream, const float *g
     const size_t nw = wskp_num_weights(&h->cfg);
     const float c1 = (float)(1.0 - std::pow((double)beta1, step)), c2 = (float)(1.0 - std::pow((double)beta2, step));
     hipError_t e = tr_adam((long)nw, h->dmaster, grad, m, v, lr, beta1, beta2, c1, c2, eps, s);
-    // the conv kernels read the weights in their own layout: repack each conv
+    // the conv kernels read the weights in their own layouts: repack each conv
     std::vector<std::pair<int, int>> d;
     conv_dims(&h->cfg, d);
     for (size_t k = 0; k < h->layers.size() && e == hipSuccess; ++k) {
@@ -1302,6 +1436,7 @@ extern "C" wskp_status_t wskp_adam(wskp_handle_t h, void *stream, const float *g
                       reinterpret_cast<float *>(static_cast<char *>(h->dweights) + lp.w_off),
                       reinterpret_cast<float *>(static_cast<char *>(h->dweights) + lp.b_off), s);
     }
+    if (e == hipSuccess) e = pack_split(h, s);
     if (e != hipSuccess) return hip_fail(e, "adam launch", WSKP_E_LAUNCH);
     return WSKP_OK;
 }

@@ -70,12 +70,12 @@ __device__ __forceinline__ void lds_sync()
 // device-resident table of n frames.
 struct FrameArg {
     const FrameDesc *table;  // device pointer, or nullptr to use `one`
-    int n;
+    int first, n;            // the launch covers frames first .. first + n - 1 of the table
     int reverse;             // walk tiles in reverse order
-    // capacity launch (graph replay): when non-null, dev_n[0] is the frame
-    // count and dev_n[1 + launch] this launch's tile count, both in device
-    // memory, and the grid is an upper bound on those tiles; workgroups
-    // beyond them exit
+    // capacity launch (graph replay): when non-null, dev_n[0] and dev_n[1] are
+    // first and n and dev_n[2 + launch] is this launch's tile count, all in
+    // device memory, and the grid is an upper bound on those tiles;
+    // workgroups beyond them exit
     const int *dev_n;
     int launch;
     FrameDesc one;
@@ -120,15 +120,16 @@ __device__ __forceinline__ int xcd_logical_id(int b, int nb)
 // that end at or before t: one round of loads per 64 frames instead of one
 // dependent load per frame.  Returns -1 past the batch's last tile.  Every
 // lane of the wave calls it with the same t; the results are wave-uniform.
+// The frames are first .. first + n - 1 of the table.
 template <typename Count>
-__device__ __forceinline__ int batch_frame(const FrameArg &fa, int n, int &t, Count count)
+__device__ __forceinline__ int batch_frame(const FrameArg &fa, int first, int n, int &t, Count count)
 {
     if (!fa.table) return t < count(fa.one.H, fa.one.W) ? 0 : -1;
     const int lane = threadIdx.x & 63;
     int base = 0;
     for (int f0 = 0; f0 < n; f0 += 64) {
         const int f = f0 + lane;
-        int c = f < n ? count(gload(&fa.table[f].H), gload(&fa.table[f].W)) : 0;
+        int c = f < n ? count(gload(&fa.table[first + f].H), gload(&fa.table[first + f].W)) : 0;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int v = __shfl_up(c, d, 64);
@@ -139,24 +140,26 @@ __device__ __forceinline__ int batch_frame(const FrameArg &fa, int n, int &t, Co
         const int valid = n - f0 < 64 ? n - f0 : 64;
         if (k < valid) {
             t = __builtin_amdgcn_readfirstlane(t - (k > 0 ? __shfl(end, k - 1, 64) : base));
-            return __builtin_amdgcn_readfirstlane(f0 + k);
+            return __builtin_amdgcn_readfirstlane(first + f0 + k);
         }
         base = __shfl(end, 63, 64);
     }
     return -1;
 }
 
-// Logical tile of workgroup b of a launch of nb workgroups, and the batch's
-// frame count n.  Capacity launches read n and the launch's tile count from
-// device memory (one load round: the two words share a cache line); there
-// the tile count is below nb, and workgroups beyond it get -1.  Then the
-// XCD-aware spread of the ids over the real tile count and the optional
-// reversal.
-__device__ __forceinline__ int batch_tile_id(const FrameArg &fa, int b, int nb, int &n)
+// Logical tile of workgroup b of a launch of nb workgroups, and the frames
+// first .. first + n - 1 it covers.  Capacity launches read these and the
+// launch's tile count from device memory (one load round: the words share a
+// cache line); there the tile count is below nb, and workgroups beyond it
+// get -1.  Then the XCD-aware spread of the ids over the real tile count and
+// the optional reversal.
+__device__ __forceinline__ int batch_tile_id(const FrameArg &fa, int b, int nb, int &first, int &n)
 {
+    first = fa.first;
     n = fa.n;
     if (fa.dev_n) {
-        const int dn = gload(fa.dev_n), dt = gload(fa.dev_n + 1 + fa.launch);
+        const int df = gload(fa.dev_n), dn = gload(fa.dev_n + 1), dt = gload(fa.dev_n + 2 + fa.launch);
+        first = __builtin_amdgcn_readfirstlane(df);
         n = __builtin_amdgcn_readfirstlane(dn);
         nb = __builtin_amdgcn_readfirstlane(dt);
         if (b >= nb) return -1;
@@ -169,7 +172,7 @@ __device__ __forceinline__ int batch_tile_id(const FrameArg &fa, int b, int nb, 
 
 enum ConvMode { CONV_PACK = 0, CONV_POOL = 1, CONV_CAT = 2, CONV_PLAIN = 3 };
 // EPI_LINEAR: bias only, NHWC fp32 store (the input gradient of a conv in
-// training runs the forward kernel with transposed, flipped weights).
+// training runs the split kernel with transposed, flipped weights).
 enum ConvEpi { EPI_RELU = 0, EPI_HEAD_SOFTPLUS = 1, EPI_HEAD_EXP = 2, EPI_LINEAR = 3 };
 enum ActType { ACT_F32 = 0, ACT_BF16 = 1 };
 
@@ -216,6 +219,14 @@ struct DecodeCfg {
 hipError_t launch_conv(const ConvLayer &L, int mode, int epi, int prec, const FrameArg &fa,
                        int blocks, hipStream_t s);
 int conv_grid(const ConvLayer &L, int n, const int *H, const int *W);
+// FP32 3x3 convs on the bf16 matrix cores (conv_split.hip): sets the layer's
+// tiling for Cin input channels (Cout set), sizes and writes its packed
+// weights (from w [Cout][Cin][3][3] on the device; dgrad: w is [Cin][Cout][3][3]
+// and the conv is its input gradient), launches it.
+void conv_split_layer(ConvLayer &L, int Cin);
+size_t conv_split_weight_bytes(int Cin, int Cout);
+hipError_t conv_split_pack(int Cin, int Cout, bool dgrad, const float *w, void *packed, hipStream_t s);
+hipError_t launch_conv_split(const ConvLayer &L, int mode, int epi, const FrameArg &fa, int blocks, hipStream_t s);
 int conv_chunk(int prec, int mode, int Cin, int C0);
 // 16-channel output blocks per workgroup for a layer with nblk blocks.
 int conv_blocks_per_group(int prec, int mode, int CK, int nblk, int level, int ks);
@@ -258,10 +269,6 @@ hipError_t tr_head_act_bwd(long P, int M, int ld, int nf, const float *grad_head
                            float *dh, hipStream_t s);
 // gm = (act > 0) g over nf frames of n values (gm may be g)
 hipError_t tr_mask(long n, int nf, const float *g, const float *act, long sa, float *gm, hipStream_t s);
-// Weights of the input-gradient conv in the fp32 forward kernels' packing
-// ([Co_pad/16][9][16][Cout_pad], 16-channel chunks): element (c, t, ci) is
-// w[c][ci][8 - t], zero beyond Co or Ci.
-hipError_t tr_pack_dgrad(int Ci, int Co, int Co_pad, int Cout_pad, const float *w, float *packed, hipStream_t s);
 // partial sums of a weight gradient over nf frames of P pixels
 size_t tr_wgrad_part_floats(long P, int Ci, int Co, int nf);
 // The conv's input: Cu channels of `up` (H/2 x W/2) upsampled x2, then Cf

@@ -1,0 +1,80 @@
+"""FP32 3x3 convs as six bf16 MFMAs (frames of at least 2^17 pixels): parity
+with the FP64 oracle at the edges of its tiles and of its range, non-finite
+inputs, and batches of frames on both sides of the size rule."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from _helpers import TOL_FP32, max_rel, rel_l2, to_dev
+from paper_2202_05977_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cfg_name,H,W", [
+    ("small", 8, 16384),      # exactly 2^17 pixels, one 8-row tile of rows
+    ("small", 364, 364),      # 4 rows and 12 columns past the last whole tile
+    ("small", 10924, 12),     # less than a tile wide
+    ("hd", 360, 376),         # three and four groups of 32 channels, 4-row tiles on the coarse levels
+])
+def test_split_convs_against_oracle(cfg_name, H, W):
+    from paper_2202_05977_amd import wskp
+    cfg = synth.CONFIGS[cfg_name]
+    blob = synth.make_weights(cfg, 4)
+    fr = synth.make_frame(5, H, W)
+    dn = wskp.Denoiser(cfg, blob, "fp32")
+    y = dn(to_dev(fr)).cpu().numpy()
+    ref = oracle.denoise(fr, blob, cfg)
+    assert H * W >= 1 << 17
+    assert rel_l2(y, ref) <= TOL_FP32 and max_rel(y, ref) <= TOL_FP32
+    dn.close()
+
+
+def test_split_convs_with_nonfinite_inputs():
+    """An infinite and a NaN albedo, and an infinite normal: the same outputs
+    are finite as with plain fp32 sums, and those agree."""
+    from paper_2202_05977_amd import wskp
+    cfg = synth.SMALL
+    blob = synth.make_weights(cfg, 4)
+    H, W = 364, 364
+    fr = synth.make_frame(6, H, W)
+    fr["albedo"][40, 50, 1] = np.inf
+    fr["albedo"][200, 300, 0] = np.nan
+    fr["normal"][300, 31, 2] = -np.inf
+    fr["normal"][100, 200, 0] = 3.4e38
+    # the same rows and columns in a frame small enough for the fp32 MFMAs
+    # (cropped well outside the net's and the filter's reach of the pixels)
+    dn = wskp.Denoiser(cfg, blob, "fp32")
+    y = dn(to_dev(fr)).cpu().numpy()
+    for cy, cx in ((40, 50), (200, 300), (300, 31), (100, 200)):
+        y0, x0 = max(0, cy // 4 * 4 - 60), max(0, cx // 4 * 4 - 60)
+        crop = {k: np.ascontiguousarray(v[y0:y0 + 124, x0:x0 + 124]) for k, v in fr.items()}
+        h, w = crop["depth"].shape[:2]
+        z = dn(to_dev(crop)).cpu().numpy()
+        # compare away from the crop's own borders
+        iy, ix = slice(28 if y0 else 0, h - 28), slice(28 if x0 else 0, w - 28)
+        a, b = y[y0:y0 + h, x0:x0 + w][iy, ix], z[iy, ix]
+        fin = np.isfinite(b)
+        assert np.array_equal(fin, np.isfinite(a)), (cy, cx)
+        assert rel_l2(a[fin], b[fin]) <= TOL_FP32, (cy, cx)
+    dn.close()
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_across_the_size_rule_equals_single_frames(graph):
+    from paper_2202_05977_amd import wskp
+    cfg = synth.SMALL
+    dn = wskp.Denoiser(cfg, synth.make_weights(cfg, 4), "fp32")
+    for sizes in ([(364, 364), (64, 96), (480, 640), (124, 36)], [(480, 640), (364, 364)], [(64, 96), (364, 364)]):
+        frames = []
+        for i, (H, W) in enumerate(sizes):
+            f = to_dev(synth.make_frame(20 + i, H, W))
+            f["out"] = torch.full_like(f["radiance"], float("nan"))
+            frames.append(f)
+        dn.batch(frames, wskp.BATCH_GRAPH if graph else 0)
+        torch.cuda.synchronize()
+        got = [f["out"].clone() for f in frames]
+        for g, f in zip(got, frames):
+            assert torch.equal(g, dn(f))
+    dn.close()

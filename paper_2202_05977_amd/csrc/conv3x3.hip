@@ -375,13 +375,6 @@ __device__ __forceinline__ void chunk_mfma(const void *As_, const void *Bs_, f32
 // values to the next level, summed in the order (2y,2x), (2y,2x+1),
 // (2y+1,2x), (2y+1,2x+1): the column partner is the neighbouring lane, the
 // row partner is block i+2 of the same lane.
-// Value held by the neighbouring lane (lane ^ 1), through a DPP quad
-// permutation [1, 0, 3, 2] (a VALU move, no LDS round trip).
-__device__ __forceinline__ float lane_xor1(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
-}
-
 // Per-lane output-channel constants of the epilogue: the bias and, for fp8,
 // the dequantisation factor of this lane's 4 channels in each block.
 template <int PREC, int NB>
@@ -595,16 +588,6 @@ __device__ __forceinline__ void load_lds16(rsrc_t r, unsigned char *lds, unsigne
 }
 
 constexpr unsigned kOutOfRange = 0x7ffffff0u;
-
-// vmcnt(N) with lgkmcnt(0): waits until at most N vector-memory loads of
-// this wave are outstanding (loads complete in order); N = 0 waits for the
-// direct-to-LDS loads of the stage.
-template <int N>
-__device__ __forceinline__ void wait_vmem()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit field");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
-}
 
 // Each wave computes HW = TH/4 output rows of the tile (both 16-pixel column
 // blocks, all NB output blocks).  For one column offset dx it reads the A
@@ -835,22 +818,17 @@ int conv_chunk(int prec, int mode, int Cin, int C0)
 #ifndef WSKP_CONV_MAX_NB
 #define WSKP_CONV_MAX_NB 4
 #endif
-#ifndef WSKP_DIRECT_MAX_NB
-#define WSKP_DIRECT_MAX_NB 2
-#endif
 // Wider groups stage and read each input tile fewer times (the A operand is
 // reused across NB blocks); narrower groups give more workgroups and a
-// smaller stage, so more of them fit a CU.  The direct-load kernel measured
-// fastest with at most two blocks (stage <= 40 KiB, four workgroups per CU)
-// and one block on the coarsest levels.  5x5 layers take one block per
-// group: their weight slices are 25/9 times larger.
-int conv_blocks_per_group(int prec, int mode, int CK, int nblk, int level, int ks)
+// smaller stage, so more of them fit a CU.  5x5 layers of the register-staged
+// kernel take one block per group: their weight slices are 25/9 times larger.
+int conv_blocks_per_group(int prec, int mode, int CK, int nblk, int ks)
 {
+    // pairs of blocks run conv_bf16.hip
+    if (uses_direct(prec, mode, CK, ks)) return nblk % 2 == 0 ? 2 : 1;
     if (ks != 3) return 1;
     if (mode == CONV_PACK) return nblk % 2 == 0 ? 2 : 1;
-    const bool direct = uses_direct(prec, mode, CK, ks);
-    if (direct && level >= WSKP_COARSE_LEVEL) return 1;
-    for (int nb = direct ? WSKP_DIRECT_MAX_NB : WSKP_CONV_MAX_NB; nb > 1; --nb)
+    for (int nb = WSKP_CONV_MAX_NB; nb > 1; --nb)
         if (nb <= 4 && nblk % nb == 0) return nb;
     return 1;
 }
@@ -922,10 +900,10 @@ static bool launch_ck_nb(const ConvLayer &L, const FrameArg &fa, int blocks, hip
     } else if constexpr (MODE == CONV_PLAIN) {
         WSKP_CASE(16, 1)
         if constexpr (PREC != 0) { WSKP_CASE(32, 1) }
-        if constexpr (PREC == 1 && EPI == EPI_RELU) { WSKP_CASE(32, 2) WSKP_CASE(32, 3) WSKP_CASE(32, 4) }
     } else {
         WSKP_CASE(16, 1) WSKP_CASE(16, 2) WSKP_CASE(16, 3) WSKP_CASE(16, 4)
-        if constexpr (PREC != 0) { WSKP_CASE(32, 1) WSKP_CASE(32, 2) WSKP_CASE(32, 3) WSKP_CASE(32, 4) }
+        if constexpr (PREC != 0) { WSKP_CASE(32, 1) }
+        if constexpr (PREC == 1 && MODE == CONV_POOL) { WSKP_CASE(32, 2) WSKP_CASE(32, 3) WSKP_CASE(32, 4) }
     }
 #undef WSKP_CASE
     return false;
@@ -954,6 +932,7 @@ hipError_t launch_conv(const ConvLayer &L, int mode, int epi, int prec, const Fr
 {
     if (blocks <= 0) return hipSuccess;
     // 5x5 layers run the register-staged kernel with one block per group
+    if (L.NB == 2 && epi == EPI_RELU && uses_direct(prec, mode, L.CK, L.ks)) return launch_conv_bf16(L, mode, fa, blocks, s);
     if (L.ks != 3 && (L.ks != 5 || L.NB != 1 || prec == 2)) return hipErrorInvalidValue;
     const bool ok = prec == 0   ? dispatch<0>(L, mode, epi, fa, blocks, s)
                     : prec == 1 ? dispatch<1>(L, mode, epi, fa, blocks, s)

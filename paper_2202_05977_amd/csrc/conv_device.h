@@ -52,29 +52,49 @@ template <> struct Elem<unsigned short> {
 };
 
 // ---- tile lookup -------------------------------------------------------------
-// Maps this workgroup to (frame, output-channel group, tile).  Returns false
-// for workgroups beyond the batch's tile count (capacity launches).
+// A tile of a conv layer: TH output rows x kConvTW columns at (y0, x0) of the
+// layer's level of frame f, output-channel group g; Hl x Wl the level's size.
+template <int TH>
+struct ConvTile {
+    int f, g, x0, y0, Hl, Wl;
+    // From logical tile t of frames first .. first + n - 1; false past the
+    // last tile.
+    __device__ __forceinline__ bool set(const ConvLayer &L, const FrameArg &fa, int first, int n, int t)
+    {
+        const int lev = L.level, groups = L.groups;
+        auto tiles = [=](int H, int W) {
+            return (((W >> lev) + kConvTW - 1) / kConvTW) * (((H >> lev) + TH - 1) / TH) * groups;
+        };
+        f = batch_frame(fa, first, n, t, tiles);
+        if (f < 0) return false;
+        const FrameDesc &fd = frame_at(fa, f);
+        Hl = fd.H >> lev;
+        Wl = fd.W >> lev;
+        const int txn = (Wl + kConvTW - 1) / kConvTW;
+        g = t % groups;
+        t /= groups;
+        x0 = (t % txn) * kConvTW;
+        y0 = (t / txn) * TH;
+        return true;
+    }
+};
+
+// Maps this workgroup to its tile.  Returns false for workgroups beyond the
+// batch's tile count (capacity launches).
 template <int TH>
 __device__ __forceinline__ bool conv_locate(const ConvLayer &L, const FrameArg &fa, int &f, int &g,
                                             int &x0, int &y0, int &Hl, int &Wl)
 {
-    const int lev = L.level, groups = L.groups;
-    auto tiles = [=](int H, int W) {
-        return (((W >> lev) + kConvTW - 1) / kConvTW) * (((H >> lev) + TH - 1) / TH) * groups;
-    };
     int first, n;
-    int t = batch_tile_id(fa, blockIdx.x, gridDim.x, first, n);
-    if (t < 0) return false;
-    f = batch_frame(fa, first, n, t, tiles);
-    if (f < 0) return false;
-    const FrameDesc &fd = frame_at(fa, f);
-    Hl = fd.H >> lev;
-    Wl = fd.W >> lev;
-    const int txn = (Wl + kConvTW - 1) / kConvTW;
-    g = t % groups;
-    t /= groups;
-    x0 = (t % txn) * kConvTW;
-    y0 = (t / txn) * TH;
+    const int t = batch_tile_id(fa, blockIdx.x, gridDim.x, first, n);
+    ConvTile<TH> c;
+    if (t < 0 || !c.set(L, fa, first, n, t)) return false;
+    f = c.f;
+    g = c.g;
+    x0 = c.x0;
+    y0 = c.y0;
+    Hl = c.Hl;
+    Wl = c.Wl;
     return true;
 }
 
@@ -179,6 +199,23 @@ __device__ __forceinline__ void pack_transform(const ConvLayer &L, float x[10])
         x[6 + ch] = (x[6 + ch] + 1.f) * 0.5f;
     }
     x[9] = fminf(fmaxf((x[9] - L.dnear) * L.dinv, 0.f), 1.f);
+}
+
+// Value held by the neighbouring lane (lane ^ 1), through a DPP quad
+// permutation [1, 0, 3, 2] (a VALU move, no LDS round trip).
+__device__ __forceinline__ float lane_xor1(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
+}
+
+// vmcnt(N) with lgkmcnt(0): waits until at most N vector-memory loads of
+// this wave are outstanding (loads complete in order); N = 0 waits for the
+// direct-to-LDS loads of the stage.
+template <int N>
+__device__ __forceinline__ void wait_vmem()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit field");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
 }
 
 }  // namespace wskp

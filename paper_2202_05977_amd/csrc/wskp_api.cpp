@@ -222,6 +222,13 @@ extern "C" size_t wskp_num_weights(const wskp_config_t *cfg)
     return n;
 }
 
+// Whether a layer runs conv_bf16.hip (direct loads, 32 output channels per
+// workgroup).
+static bool runs_conv_bf16(int prec, const LayerPlan &lp)
+{
+    return lp.L.NB == 2 && lp.epi == EPI_RELU && conv_uses_direct(prec, lp.mode, lp.L.CK, lp.L.ks);
+}
+
 // Packs OIHW fp32 weights into the order the kernels read (see conv3x3.hip).
 // fp8: per output channel, w is divided by s_w[co] = max|w_co| / 448 before
 // rounding; dq[co] receives s_in * s_w[co], the factor that turns the
@@ -274,6 +281,22 @@ static void pack_layer(int prec, const LayerPlan &lp, const float *w, std::vecto
         // in LDS bank-friendly).  Direct-to-LDS kernel: KR = NK*32, and in
         // row co the 8-element groups are stored at position g ^ (2 * ((co
         // >> 2) & 1)), the bank-conflict-free order that kernel reads.
+        if (runs_conv_bf16(prec, lp)) {
+            // fragments [group of 32 channels][chunk][tap][half of the
+            // chunk], in each lane (h, j)'s 8 values for output channel j of
+            // the group and input channels 8 h .. 8 h + 7 of the half
+            const int groups = Cout / 32;
+            out.assign((size_t)nch * L.Cout_pad * T * CK * 2, 0);
+            uint16_t *o = reinterpret_cast<uint16_t *>(out.data());
+            for (int g = 0; g < groups; ++g)
+                for (int cc = 0; cc < nch; ++cc)
+                    for (int t = 0; t < T; ++t)
+                        for (int i = 0; i < 1024; ++i) {
+                            const int half = i >> 9, lane = (i >> 3) & 63;
+                            *o++ = host_bf16(W(g * 32 + (lane & 31), cc * CK + half * 16 + (lane >> 5) * 8 + (i & 7), t));
+                        }
+            return;
+        }
         const bool direct = conv_uses_direct(prec, lp.mode, CK, L.ks);
         const int NK = (T * CK + 31) / 32, KR = direct ? NK * 32 : NK * 32 + 8;
         out.assign((size_t)nch * L.Cout_pad * KR * 2, 0);
@@ -403,7 +426,7 @@ extern "C" wskp_status_t wskp_create(const wskp_config_t *cfg, const float *host
         c.Cin_pad = (Cin + c.CK - 1) / c.CK * c.CK;
         c.Cout = Cout;
         const int nblk = (Cout + 15) / 16;
-        c.NB = conv_blocks_per_group(h->prec, mode, c.CK, nblk, level, ks);
+        c.NB = conv_blocks_per_group(h->prec, mode, c.CK, nblk, ks);
         c.groups = nblk / c.NB;
         c.th = conv_tile_rows(h->prec, mode, c.CK, level, pool_idx >= 0, ks);
         c.pool_idx = pool_idx;
@@ -724,6 +747,7 @@ static std::vector<ConvGroup> plan_convs(const wskp_ctx *h, int n, const int *Hs
         ConvGroup g{f, e - f, {}};
         for (const LayerPlan &lp : split ? h->split : h->layers) {
             ConvLaunch c{lp.L, lp.mode, lp.epi, split, 0};
+            if (runs_conv_bf16(h->prec, lp)) c.L.th = conv_bf16_rows(c.L, g.n, Hs + f, Ws + f);
             c.blocks = conv_grid(c.L, g.n, Hs + f, Ws + f);
             // 4-row tiles where 8-row ones leave CUs without their two workgroups
             if (split && c.blocks < 512) {

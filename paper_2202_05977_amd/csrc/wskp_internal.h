@@ -229,7 +229,10 @@ hipError_t conv_split_pack(int Cin, int Cout, bool dgrad, const float *w, void *
 hipError_t launch_conv_split(const ConvLayer &L, int mode, int epi, const FrameArg &fa, int blocks, hipStream_t s);
 int conv_chunk(int prec, int mode, int Cin, int C0);
 // 16-channel output blocks per workgroup for a layer with nblk blocks.
-int conv_blocks_per_group(int prec, int mode, int CK, int nblk, int level, int ks);
+int conv_blocks_per_group(int prec, int mode, int CK, int nblk, int ks);
+// bf16 layers of conv_bf16.hip: tile rows for n frames, and the launch
+int conv_bf16_rows(const ConvLayer &L, int n, const int *H, const int *W);
+hipError_t launch_conv_bf16(const ConvLayer &L, int mode, const FrameArg &fa, int blocks, hipStream_t s);
 // Decode + fusion + remodulation over frames of fa (denoise mode: c and mod
 // derive from r, a) -- or over plain tensors (decode mode).
 hipError_t launch_decode_frames(const DecodeCfg &dc, const FrameArg &fa, int blocks, hipStream_t s);

@@ -35,13 +35,30 @@ static_assert(kDTY % 8 == 0, "8 row groups of kDTY/8 rows");
 #define WSKP_DECODE_MIN_WG 4
 #endif
 
+// Equal-size frames as plain tensors.  MR (the multi-resolution
+// reconstruction): one frame at `levels` resolutions, level l's head record and
+// output at head_l[l] and out_l[l], the irradiance c at full resolution.
+struct DecodeTensors {
+    int N, H, W;
+    const float *head, *c, *mod;   // mod may be null
+    float *out;
+    // adjoint only
+    const float *g;     // dL/dout [N,H,W,3]
+    float *grad_head;   // [N,H,W,2M]
+    float4 *scratch;    // [N,M,H,W] x (u_0, u_1, u_2, dS)
+    float *dlogit;      // [N,M,H,W]: the logits' gradients, pass A to pass B
+    // MR only
+    int levels;
+    const float *head_l[kMaxLevels];
+    float *out_l[kMaxLevels];
+};
+
+// One tile's frame: size, origin and pointers.
 struct DecodeIO {
-    int H, W;
-    const float *head;  // map j of pixel q at head[q * hs_pix + j * hs_map]
-    size_t hs_pix, hs_map;
-    const float *r, *a; // frames form
-    const float *c;     // tensors form
-    const float *mod;   // tensors form, may be null
+    int H, W, x0, y0;
+    int level, W0;      // MR: the level, the full-resolution width
+    const float *head;  // interleaved [H][W][2M]
+    const float *c, *mod;
     float *out;
     const float *g;
     float *grad_head;
@@ -49,60 +66,49 @@ struct DecodeIO {
     float *dlogit;
 };
 
-struct DecodeTensors {
-    int N, H, W;
-    const float *head, *c, *mod;
-    float *out;
-    // adjoint only
-    const float *g;     // dL/dout [N,H,W,3]
-    float *grad_head;   // [N,H,W,2M]
-    float4 *scratch;    // [N,M,H,W] x (u_0, u_1, u_2, dS)
-    float *dlogit;      // [N,M,H,W]: the logits' gradients, pass A to pass B
-};
-
-// Tile u of nbk (u in launch order) -> frame, tile origin and I/O pointers.
-template <bool FRAMES>
-__device__ __forceinline__ bool decode_locate_at(const DecodeCfg &dc, const FrameArg &fa,
-                                                 const DecodeTensors &dt, int u, int nbk,
-                                                 DecodeIO &io, int &x0, int &y0)
+__device__ __host__ __forceinline__ int decode_tiles(int H, int W)
 {
-    const int twoM = 2 * dc.M;
-    auto tiles = [](int H, int W) { return ((W + kDTX - 1) / kDTX) * ((H + kDTY - 1) / kDTY); };
-    int t = xcd_logical_id(u, nbk);
-    if constexpr (FRAMES) {
-        int first, n;
-        t = batch_tile_id(fa, u, nbk, first, n);
-        if (t < 0) return false;
-        const int f = batch_frame(fa, first, n, t, tiles);
-        if (f < 0) return false;
-        const FrameDesc &fd = frame_at(fa, f);
-        io.H = fd.H;
-        io.W = fd.W;
-        io.head = fd.head;              // planar [2M][H][W] (written by the head conv)
-        io.hs_pix = 1;
-        io.hs_map = (size_t)fd.H * fd.W;
-        io.r = fd.r;
-        io.a = fd.a;
-        io.c = nullptr;
-        io.mod = nullptr;
-        io.out = fd.out;
-        io.g = nullptr;
-        io.grad_head = nullptr;
-        io.scratch = nullptr;
-        io.dlogit = nullptr;
+    return ((W + kDTX - 1) / kDTX) * ((H + kDTY - 1) / kDTY);
+}
+
+// This workgroup's tile; false past the last.
+template <bool MR>
+__device__ __forceinline__ bool decode_locate(const DecodeCfg &dc, const DecodeTensors &dt, DecodeIO &io)
+{
+    int t, f = 0;
+    io = DecodeIO{};
+    io.H = dt.H;
+    io.W = dt.W;
+    io.W0 = dt.W;
+    if constexpr (MR) {
+        // the coarse levels' tiles, which stage 4 and 16 times the irradiance,
+        // first and dealt over the XCDs; then the finest level's, a
+        // contiguous run to each XCD
+        const int n0 = decode_tiles(dt.H, dt.W), nc = (int)gridDim.x - n0;
+        t = blockIdx.x;
+        if (t >= nc) {
+            t = xcd_logical_id(t - nc, n0);
+        } else {
+            for (io.level = dt.levels - 1;; --io.level) {
+                io.H = dt.H >> io.level;
+                io.W = dt.W >> io.level;
+                const int cnt = decode_tiles(io.H, io.W);
+                if (t < cnt || io.level <= 1) break;
+                t -= cnt;
+            }
+        }
+        io.head = dt.head_l[io.level];
+        io.out = dt.out_l[io.level];
+        io.c = dt.c;
     } else {
         // equal-size frames: the frame index is a division
-        const int cnt = tiles(dt.H, dt.W);
-        const int f = t / cnt;
+        t = xcd_logical_id(blockIdx.x, gridDim.x);
+        const int cnt = decode_tiles(dt.H, dt.W), twoM = 2 * dc.M;
+        f = t / cnt;
         if (f >= dt.N) return false;
         t -= f * cnt;
         const size_t P = (size_t)dt.H * dt.W;
-        io.H = dt.H;
-        io.W = dt.W;
-        io.head = dt.head + (size_t)f * P * twoM;   // interleaved [H][W][2M]
-        io.hs_pix = twoM;
-        io.hs_map = 1;
-        io.r = io.a = nullptr;
+        io.head = dt.head + (size_t)f * P * twoM;
         io.c = dt.c + (size_t)f * P * 3;
         io.mod = dt.mod ? dt.mod + (size_t)f * P * 3 : nullptr;
         io.out = dt.out ? dt.out + (size_t)f * P * 3 : nullptr;
@@ -112,20 +118,36 @@ __device__ __forceinline__ bool decode_locate_at(const DecodeCfg &dc, const Fram
         io.dlogit = dt.dlogit ? dt.dlogit + (size_t)f * P * dc.M : nullptr;
     }
     const int txn = (io.W + kDTX - 1) / kDTX;
-    x0 = (t % txn) * kDTX;
-    y0 = (t / txn) * kDTY;
+    io.x0 = (t % txn) * kDTX;
+    io.y0 = (t / txn) * kDTY;
     return true;
 }
 
-template <bool FRAMES>
-__device__ __forceinline__ bool decode_locate(const DecodeCfg &dc, const FrameArg &fa,
-                                              const DecodeTensors &dt, DecodeIO &io, int &x0,
-                                              int &y0)
+// The irradiance of pixel (y, x) of MR level L: L 2x2 means of the full image c
+// (width W0), each taken as pool2_kernel takes it, from the 2^L rows of 2^L
+// pixels that it covers.
+template <int L>
+__device__ __forceinline__ void pooled_c(const float *c, int W0, int y, int x, float *v)
 {
-    return decode_locate_at<FRAMES>(dc, fa, dt, blockIdx.x, gridDim.x, io, x0, y0);
+    constexpr int S = 1 << L;
+    float b[S][3 * S];
+#pragma unroll
+    for (int r = 0; r < S; ++r) load_floats<3 * S>(c + ((size_t)(S * y + r) * W0 + S * x) * 3, b[r]);
+#pragma unroll
+    for (int s = S / 2; s >= 1; s /= 2)
+#pragma unroll
+        for (int r = 0; r < s; ++r)
+#pragma unroll
+            for (int k = 0; k < s; ++k)
+#pragma unroll
+                for (int ch = 0; ch < 3; ++ch)
+                    b[r][3 * k + ch] = 0.25f * (((b[2 * r][6 * k + ch] + b[2 * r][6 * k + 3 + ch]) + b[2 * r + 1][6 * k + ch]) +
+                                                b[2 * r + 1][6 * k + 3 + ch]);
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) v[ch] = b[0][ch];
 }
 
-enum DecodeKind { DK_FRAMES = 0, DK_TENSORS = 1, DK_ADJ_A = 2 };
+enum DecodeKind { DK_TENSORS = 1, DK_ADJ_A = 2, DK_MR = 3 };
 
 // e^x for the softmax numerators (x = l_i - max_j l_j <= 0): the hardware
 // 2^x of x log2(e) instead of the library expf.  Relative error about
@@ -275,31 +297,12 @@ __device__ __forceinline__ void halo_pixels(int x0, int y0, int R, int HX, int H
 // largest, radiance and albedo, stay below 3.3e9 bytes); such loads read 0.
 constexpr unsigned kNoPixel = 0xfffffff0u;
 
-// Frames form: weight map i (a plane of the head record) at this thread's
-// halo slots, from byte offsets o1 (4 * pixel, or kNoPixel: reads 0).
-template <int RM>
-__device__ __forceinline__ void load_w_frames(const DecodeIO &io, int i, const unsigned *o1, float *w)
-{
-    const unsigned P = (unsigned)(io.H * io.W);
-    const rsrc_t rs = make_rsrc(io.head + (size_t)i * P, P * 4u);
-#pragma unroll
-    for (int k = 0; k < max_pix<RM>(); ++k)
-        w[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o1[k], 0, 0));
-}
-
-// Loads weight map i at this thread's halo pixels, unconditionally (pixels
-// outside the image read pixel 0; the caller masks them with gp < 0).
-template <int M, int RM>
-__device__ __forceinline__ void load_w(const DecodeIO &io, int i, const int *gp, float *w)
-{
-#pragma unroll
-    for (int k = 0; k < max_pix<RM>(); ++k)
-        w[k] = gload(io.head + (size_t)(gp[k] >= 0 ? gp[k] : 0) * io.hs_pix + i * io.hs_map);
-}
-
 // Dynamic LDS: product plane float4 [HXY] (W_i, W_i c) rebuilt for each
 // kernel size, row sums float4 [(kDTY+2R)][kHB].
-//   DK_FRAMES / DK_TENSORS: forward, writes out.
+//   DK_TENSORS: forward, writes out.
+//   DK_MR: forward of every level of the multi-resolution reconstruction in
+//     one launch (no remodulation); coarser levels take the means of c while
+//     staging, so no pooled image is written.
 //   DK_ADJ_A: first half of the vector-Jacobian product.  Per centre p,
 //     with dF = g * mod, da_i = <dF, out_i>:
 //       dlogit_i   = alpha_i (da_i - sum_j alpha_j da_j)
@@ -308,16 +311,23 @@ __device__ __forceinline__ void load_w(const DecodeIO &io, int i, const int *gp,
 //     (u_i, dS_i) and dlogit_i go to scratch (planes per size, coalesced
 //     stores); decode_adj_b_kernel box-sums (u_i, dS_i) and writes each
 //     pixel's whole grad_head record.
+// A pixel's M weights (consecutive in its head record) are loaded once, with
+// the irradiance, in the widest loads, and so are a centre's logits: map by
+// map, as one 4-byte load per lane and size 8 M bytes apart, every size read
+// the lines of the whole record again and waited for them.  M = 6, k = 3..13,
+// 715 x 1273: 43.3 -> 31.0 us (76 MB, 2.5 TB/s); M = 5, 8 x 256 x 256: 19.9 ->
+// 15.2.  The window sums and their LDS traffic take what the memory (15 us of
+// the 31) does not.  DK_MR, 720p, 3 levels of k = 3, 5: 19.6 us in one launch
+// instead of 33.5 in five (two pools, three decodes).
 template <int M, int KIND, int RM>
-__global__ __launch_bounds__(kThreads, WSKP_DECODE_MIN_WG) void decode_fwd_kernel(DecodeCfg dc, FrameArg fa,
-                                                               DecodeTensors dt)
+__global__ __launch_bounds__(kThreads, M <= 5 ? WSKP_DECODE_MIN_WG : (KIND == DK_ADJ_A ? 2 : 3)) void
+decode_fwd_kernel(DecodeCfg dc, DecodeTensors dt)
 {
-    constexpr bool FRAMES = KIND == DK_FRAMES;
-    constexpr bool ADJ = KIND == DK_ADJ_A;
+    constexpr bool ADJ = KIND == DK_ADJ_A, MR = KIND == DK_MR;
     extern __shared__ float4 lds4[];
     DecodeIO io;
-    int x0, y0;
-    if (!decode_locate<FRAMES>(dc, fa, dt, io, x0, y0)) return;
+    if (!decode_locate<MR>(dc, dt, io)) return;
+    const int x0 = io.x0, y0 = io.y0;
 
     const int R = dc.R;
     const int HX = halo_stride(R), HXY = HX * (kDTY + 2 * R);
@@ -329,77 +339,47 @@ __global__ __launch_bounds__(kThreads, WSKP_DECODE_MIN_WG) void decode_fwd_kerne
     constexpr int kMaxPix = max_pix<RM>();
     int gp[kMaxPix];
     halo_pixels<RM>(x0, y0, R, HX, HXY, H, W, gp);
-    // irradiance of this thread's halo pixels, kept in registers; c = r /
-    // (a + eps_a) uses the hardware reciprocal.  The weight map of each size
-    // is fetched one size ahead.
+    // irradiance and weights of this thread's halo pixels, kept in registers.
     // All loads are unconditional (pixels outside the image or the halo read
     // pixel 0 and are masked afterwards), so that every request is in flight
     // before the first result is used.
-    // The frames form uses buffer loads from precomputed byte offsets: a
-    // slot outside the image gets kNoPixel and reads zeros (c = 0 * rcp(eps_a)
-    // = 0, W = 0), so nothing needs masking afterwards.
-    float cv[kMaxPix][3], av[FRAMES ? kMaxPix : 1][3], wv[kMaxPix];
-    unsigned o1[FRAMES ? kMaxPix : 1];
-    if constexpr (FRAMES) {
-        const unsigned P = (unsigned)(H * W);
-        const rsrc_t rr = make_rsrc(io.r, P * 12u), ra = make_rsrc(io.a, P * 12u);
+    float cv[kMaxPix][3], wv[kMaxPix][M];
 #pragma unroll
-        for (int k = 0; k < kMaxPix; ++k) {
-            const unsigned o3 = gp[k] >= 0 ? (unsigned)gp[k] * 12u : kNoPixel;
-            o1[k] = gp[k] >= 0 ? (unsigned)gp[k] * 4u : kNoPixel;
-            const auto r3 = __builtin_amdgcn_raw_buffer_load_b96(rr, o3, 0, 0);
-            const auto a3 = __builtin_amdgcn_raw_buffer_load_b96(ra, o3, 0, 0);
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                cv[k][ch] = __uint_as_float(r3[ch]);
-                av[k][ch] = __uint_as_float(a3[ch]);
-            }
+    for (int k = 0; k < kMaxPix; ++k) {
+        const size_t q = (size_t)(gp[k] >= 0 ? gp[k] : 0);
+        if (!MR || io.level == 0) {
+            load_floats<3>(io.c + q * 3, cv[k]);
+        } else {
+            const int y = (int)q / W, x = (int)q - y * W;
+            if (io.level == 1) pooled_c<1>(io.c, io.W0, y, x, cv[k]);
+            else pooled_c<2>(io.c, io.W0, y, x, cv[k]);
         }
-        load_w_frames<RM>(io, 0, o1, wv);
-    } else {
-#pragma unroll
-        for (int k = 0; k < kMaxPix; ++k) {
-            const size_t q = (size_t)(gp[k] >= 0 ? gp[k] : 0) * 3;
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) cv[k][ch] = gload(io.c + q + ch);
-        }
-        load_w<M, RM>(io, 0, gp, wv);
+        load_floats<M>(io.head + q * (2 * M), wv[k]);
     }
-#pragma unroll
-    for (int k = 0; k < kMaxPix; ++k)
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            if constexpr (FRAMES)
-                cv[k][ch] *= __builtin_amdgcn_rcpf(av[FRAMES ? k : 0][ch] + dc.eps_albedo);
-            else
-                cv[k][ch] = gp[k] >= 0 ? cv[k][ch] : 0.f;
-        }
-
-    // Fusion (Eq. 5) of this thread's kRun centres (column tx, rows
-    // kRun*ty + o).  Forward: softmax numerators exp(l_i - max_j l_j) weight
-    // the filtered values as they are produced and the sum of the
-    // numerators divides once at the end; no per-size state is kept, so the
-    // size loop need not be unrolled.  Adjoint: the normalised alpha_i are
-    // kept for the gradient.
-    const float *lp[kRun];
-    unsigned lo[FRAMES ? kRun : 1];   // frames: byte offset of the centre in a plane
-    // frames: logit i of this thread's centres, from plane M + i by buffer load
-    auto logit_frames = [&](int i, int o) {
-        const unsigned P = (unsigned)(H * W);
-        const rsrc_t rs = make_rsrc(io.head + (size_t)(M + i) * P, P * 4u);
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, lo[FRAMES ? o : 0], 0, 0));
-    };
-    float lmax[kRun], esum[kRun], F[kRun][3];
-    float alpha[ADJ ? kRun : 1][ADJ ? M : 1];
+    // the logits of this thread's centres (column tx, rows kRun*ty + o)
+    float lg[kRun][M];
 #pragma unroll
     for (int o = 0; o < kRun; ++o) {
         const int y = y0 + kRun * ty + o, x = x0 + tx;
         const bool in = y < H && x < W;
-        lp[o] = io.head + ((size_t)(in ? y : 0) * W + (in ? x : 0)) * io.hs_pix + M * io.hs_map;
-        if constexpr (FRAMES) lo[o] = in ? (unsigned)(y * W + x) * 4u : 0u;
+        load_floats<M>(io.head + ((size_t)(in ? y : 0) * W + (in ? x : 0)) * (2 * M) + M, lg[o]);
+    }
+#pragma unroll
+    for (int k = 0; k < kMaxPix; ++k)
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) cv[k][ch] = gp[k] >= 0 ? cv[k][ch] : 0.f;
+
+    // Fusion (Eq. 5).  Forward: softmax numerators exp(l_i - max_j l_j) weight
+    // the filtered values as they are produced and the sum of the numerators
+    // divides once at the end.  Adjoint: the normalised alpha_i are kept for
+    // the gradient.
+    float lmax[kRun], esum[kRun], F[kRun][3];
+    float alpha[ADJ ? kRun : 1][ADJ ? M : 1];
+#pragma unroll
+    for (int o = 0; o < kRun; ++o) {
         float m = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < M; ++i) m = fmaxf(m, FRAMES ? logit_frames(i, o) : gload(lp[o] + i * io.hs_map));
+        for (int i = 0; i < M; ++i) m = fmaxf(m, lg[o][i]);
         lmax[o] = m;
         esum[o] = 0.f;
         F[o][0] = F[o][1] = F[o][2] = 0.f;
@@ -407,7 +387,7 @@ __global__ __launch_bounds__(kThreads, WSKP_DECODE_MIN_WG) void decode_fwd_kerne
             float sum = 0.f;
 #pragma unroll
             for (int i = 0; i < M; ++i) {
-                alpha[o][i] = expf(gload(lp[o] + i * io.hs_map) - m);
+                alpha[o][i] = expf(lg[o][i] - m);
                 sum += alpha[o][i];
             }
             const float inv = 1.f / sum;
@@ -421,24 +401,11 @@ __global__ __launch_bounds__(kThreads, WSKP_DECODE_MIN_WG) void decode_fwd_kerne
 
     // one kernel size: product plane, window sums, normalisation, fusion
     auto size_step = [&](int i) {
-        // this size's logits of the thread's centres, requested first so
-        // that the window sums hide their latency
-        float lgv[ADJ ? 1 : kRun];
-        if constexpr (!ADJ) {
-#pragma unroll
-            for (int o = 0; o < kRun; ++o) lgv[o] = FRAMES ? logit_frames(i, o) : gload(lp[o] + i * io.hs_map);
-        }
-        // product plane of this size from this thread's registers, then
-        // fetch the next size's weights
 #pragma unroll
         for (int k = 0; k < kMaxPix; ++k) {
             const int p = tid + k * kThreads;
-            const float w = (FRAMES || gp[k] >= 0) ? wv[k] : 0.f;
+            const float w = gp[k] >= 0 ? wv[k][i] : 0.f;
             if (p < HXY) pr[p] = make_float4(w, w * cv[k][0], w * cv[k][1], w * cv[k][2]);
-        }
-        if (i + 1 < M) {
-            if constexpr (FRAMES) load_w_frames<RM>(io, i + 1, o1, wv);
-            else load_w<M, RM>(io, i + 1, gp, wv);
         }
         lds_sync();
         float4 acc[kRun];
@@ -455,7 +422,7 @@ __global__ __launch_bounds__(kThreads, WSKP_DECODE_MIN_WG) void decode_fwd_kerne
                 outv[o][i][2] = o2;
                 Sv[o][i] = acc[o].x;
             } else {
-                const float e = exp_softmax(lgv[o] - lmax[o]);
+                const float e = exp_softmax(lg[o][i] - lmax[o]);
                 esum[o] += e;
                 F[o][0] += e * o0;
                 F[o][1] += e * o1;
@@ -467,24 +434,17 @@ __global__ __launch_bounds__(kThreads, WSKP_DECODE_MIN_WG) void decode_fwd_kerne
 #pragma unroll
         for (int i = 0; i < M; ++i) size_step(i);
     } else {
-#pragma unroll 1
+#pragma unroll
         for (int i = 0; i < M - 1; ++i) size_step(i);
         // the centres' remodulation factors are requested before the last
         // size's window sums, which hide their latency (centres outside the
         // image read pixel 0 and are not stored)
 #pragma unroll
         for (int o = 0; o < kRun; ++o) {
-            if constexpr (FRAMES) {
-                const unsigned P = (unsigned)(H * W);
-                const auto a3 = __builtin_amdgcn_raw_buffer_load_b96(make_rsrc(io.a, P * 12u), lo[o] * 3u, 0, 0);
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) mv[o][ch] = __uint_as_float(a3[ch]) + dc.eps_albedo;
-            } else {
-                const int y = y0 + kRun * ty + o, x = x0 + tx;
-                const size_t pix = (y < H && x < W) ? (size_t)y * W + x : 0;
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) mv[o][ch] = io.mod ? gload(io.mod + pix * 3 + ch) : 1.f;
-            }
+            const int y = y0 + kRun * ty + o, x = x0 + tx;
+            const size_t pix = (y < H && x < W) ? (size_t)y * W + x : 0;
+            if (!MR && io.mod) load_floats<3>(io.mod + pix * 3, mv[o]);
+            else mv[o][0] = mv[o][1] = mv[o][2] = 1.f;
         }
         size_step(M - 1);
 #pragma unroll
@@ -596,7 +556,7 @@ __global__ __launch_bounds__(kFThreads, 4) void decode_tile_kernel(DecodeCfg dc,
     const int tid = threadIdx.x;
 
     // ---- tile -> frame, origin, I/O
-    DecodeIO io;
+    struct { int H, W; const float *head, *r, *a; float *out; } io;
     int x0, y0;
     {
         auto tiles = [&](int H, int W) { return ((W + TW - 1) / TW) * ((H + TH - 1) / TH); };
@@ -609,12 +569,8 @@ __global__ __launch_bounds__(kFThreads, 4) void decode_tile_kernel(DecodeCfg dc,
         io.H = fd.H;
         io.W = fd.W;
         io.head = fd.head;
-        io.hs_pix = 1;
-        io.hs_map = (size_t)fd.H * fd.W;
         io.r = fd.r;
         io.a = fd.a;
-        io.c = nullptr;
-        io.mod = nullptr;
         io.out = fd.out;
         const int txn = (io.W + TW - 1) / TW;
         x0 = (t % txn) * TW;
@@ -864,10 +820,9 @@ __global__ __launch_bounds__(kThreads) void decode_adj_b_kernel(DecodeCfg dc, De
                                                                  float *grad_c)
 {
     extern __shared__ float4 lds4[];
-    FrameArg fa{};
     DecodeIO io;
-    int x0, y0;
-    if (!decode_locate<false>(dc, fa, dt, io, x0, y0)) return;
+    if (!decode_locate<false>(dc, dt, io)) return;
+    const int x0 = io.x0, y0 = io.y0;
     const int R = dc.R;
     const int HX = halo_stride(R), HXY = HX * (kDTY + 2 * R);
     float4 *st = lds4;
@@ -888,13 +843,9 @@ __global__ __launch_bounds__(kThreads) void decode_adj_b_kernel(DecodeCfg dc, De
     for (int o = 0; o < kRun; ++o) {
         const int y = y0 + kRun * ty + o, x = x0 + tx;
         const size_t pix = (y < H && x < W) ? (size_t)y * W + x : 0;
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            cvv[o][ch] = gload(io.c + pix * 3 + ch);
-            dcv[o][ch] = 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < M; ++i) wvv[o][i] = gload(io.head + pix * (2 * M) + i);
+        load_floats<3>(io.c + pix * 3, cvv[o]);
+        dcv[o][0] = dcv[o][1] = dcv[o][2] = 0.f;
+        load_floats<M>(io.head + pix * (2 * M), wvv[o]);
     }
 #pragma unroll
     for (int i = 0; i < M; ++i) {
@@ -968,8 +919,7 @@ static void allow_lds(K kernel, size_t bytes)
 }
 
 template <int KIND>
-static hipError_t launch_decode(const DecodeCfg &dc, const FrameArg &fa, const DecodeTensors &dt,
-                                int blocks, hipStream_t s)
+static hipError_t launch_decode(const DecodeCfg &dc, const DecodeTensors &dt, int blocks, hipStream_t s)
 {
     if (blocks <= 0) return hipSuccess;
     const size_t lds = decode_lds_bytes(dc);
@@ -981,11 +931,11 @@ static hipError_t launch_decode(const DecodeCfg &dc, const FrameArg &fa, const D
         if (r5) {                                                                                  \
             allow_lds(decode_fwd_kernel<m, KIND, 5>, lds);                                         \
             hipLaunchKernelGGL((decode_fwd_kernel<m, KIND, 5>), dim3(blocks), dim3(kThreads), lds, \
-                               s, dc, fa, dt);                                                     \
+                               s, dc, dt);                                                         \
         } else {                                                                                   \
             allow_lds(decode_fwd_kernel<m, KIND, 7>, lds);                                         \
             hipLaunchKernelGGL((decode_fwd_kernel<m, KIND, 7>), dim3(blocks), dim3(kThreads), lds, \
-                               s, dc, fa, dt);                                                     \
+                               s, dc, dt);                                                         \
         }                                                                                          \
         break;
         WSKP_M(1) WSKP_M(2) WSKP_M(3) WSKP_M(4) WSKP_M(5) WSKP_M(6) WSKP_M(7) WSKP_M(8)
@@ -1058,10 +1008,33 @@ hipError_t launch_decode_tensors(const DecodeCfg &dc, int N, int H, int W, const
 {
     // the 32 x 16-tile kernel: on equal-size stacks it measured faster than
     // the 40 x 45 tile kernel (29 vs 35 us for 8 x 256^2, 42 vs 45 us at 720p)
-    DecodeTensors dt{N, H, W, head, c, mod, out, nullptr, nullptr, nullptr, nullptr};
-    FrameArg fa{};
-    const int blocks = N * ((W + kDTX - 1) / kDTX) * ((H + kDTY - 1) / kDTY);
-    return launch_decode<DK_TENSORS>(dc, fa, dt, blocks, s);
+    DecodeTensors dt{};
+    dt.N = N;
+    dt.H = H;
+    dt.W = W;
+    dt.head = head;
+    dt.c = c;
+    dt.mod = mod;
+    dt.out = out;
+    return launch_decode<DK_TENSORS>(dc, dt, N * decode_tiles(H, W), s);
+}
+
+hipError_t launch_decode_levels(const DecodeCfg &dc, int levels, int H, int W, const float *const *heads,
+                                const float *c, float *const *outs, hipStream_t s)
+{
+    DecodeTensors dt{};
+    dt.N = 1;
+    dt.H = H;
+    dt.W = W;
+    dt.c = c;
+    dt.levels = levels;
+    int blocks = 0;
+    for (int l = 0; l < levels; ++l) {
+        dt.head_l[l] = heads[l];
+        dt.out_l[l] = outs[l];
+        blocks += decode_tiles(H >> l, W >> l);
+    }
+    return launch_decode<DK_MR>(dc, dt, blocks, s);
 }
 
 size_t decode_backward_scratch_bytes(const DecodeCfg &dc, int N, int H, int W)
@@ -1074,12 +1047,19 @@ hipError_t launch_decode_backward(const DecodeCfg &dc, int N, int H, int W, cons
                                   const float *c, const float *mod, const float *g,
                                   float *grad_head, float *grad_c, void *scratch, hipStream_t s)
 {
-    FrameArg fa{};
-    float4 *s4 = reinterpret_cast<float4 *>(scratch);
-    DecodeTensors dt{N, H, W, head, c, mod, nullptr, g, grad_head, s4,
-                     reinterpret_cast<float *>(s4 + (size_t)N * dc.M * H * W)};
-    const int blocks = N * ((W + kDTX - 1) / kDTX) * ((H + kDTY - 1) / kDTY);
-    hipError_t e = launch_decode<DK_ADJ_A>(dc, fa, dt, blocks, s);
+    DecodeTensors dt{};
+    dt.N = N;
+    dt.H = H;
+    dt.W = W;
+    dt.head = head;
+    dt.c = c;
+    dt.mod = mod;
+    dt.g = g;
+    dt.grad_head = grad_head;
+    dt.scratch = reinterpret_cast<float4 *>(scratch);
+    dt.dlogit = reinterpret_cast<float *>(dt.scratch + (size_t)N * dc.M * H * W);
+    const int blocks = N * decode_tiles(H, W);
+    hipError_t e = launch_decode<DK_ADJ_A>(dc, dt, blocks, s);
     if (e != hipSuccess) return e;
     const size_t lds = adj_b_lds_bytes(dc);
     const bool r5 = dc.R <= 5;

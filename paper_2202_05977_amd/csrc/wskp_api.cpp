@@ -1558,23 +1558,22 @@ extern "C" wskp_status_t wskp_mr_reconstruct(wskp_handle_t h, void *stream, int 
         return WSKP_OK;
     }
     float *base = static_cast<float *>(ws);
-    // pooled irradiance of every coarser level
+    // the levels filtered with their own heads (no remodulation): the first
+    // three in one launch, which pools c while staging; deeper ones, each at
+    // most 1/64 of the frame, from images pooled by launches of their own
+    float *fl[WSKP_MAX_LEVELS];
+    for (int l = 0; l < L; ++l) fl[l] = base + f[l];
+    const int joint = std::min(L, 3);
     const float *cl = c;
-    for (int l = 1; l < L && e == hipSuccess; ++l) {
+    for (int l = 1; l < L && L > joint && e == hipSuccess; ++l) {
         e = launch_pool2(H >> (l - 1), W >> (l - 1), cl, base + cs[l], s);
         cl = base + cs[l];
     }
-    // every level filtered with its own head (no remodulation)
-    for (int l = 0; l < L && e == hipSuccess; ++l)
-        e = launch_decode_tensors(h->dc, 1, H >> l, W >> l, heads[l], l ? base + cs[l] : c, nullptr,
-                                  base + f[l], s);
+    if (e == hipSuccess) e = launch_decode_levels(h->dc, joint, H, W, heads, c, fl, s);
+    for (int l = joint; l < L && e == hipSuccess; ++l)
+        e = launch_decode_tensors(h->dc, 1, H >> l, W >> l, heads[l], base + cs[l], nullptr, fl[l], s);
     // Eq. 7 from the coarsest; the finest blend is remodulated into out
-    const float *coarse = base + f[L - 1];
-    for (int l = L - 2; l >= 0 && e == hipSuccess; --l) {
-        float *dst = l ? base + o[l] : out;
-        e = launch_mr_blend(H >> l, W >> l, base + f[l], coarse, alphas[l], l ? nullptr : mod, dst, s);
-        coarse = dst;
-    }
+    if (e == hipSuccess) e = launch_mr_blend_all(L, H, W, fl, alphas, mod, out, s);
     if (e != hipSuccess) return hip_fail(e, "multi-resolution launch", WSKP_E_LAUNCH);
     return WSKP_OK;
 }

@@ -38,6 +38,41 @@ __device__ __forceinline__ void gstore(T *p, T v)
 {
     *(__attribute__((address_space(1))) T *)p = v;
 }
+// N consecutive floats from an address of any float alignment, in the widest
+// loads that N allows (the hardware takes them at 4-byte alignment).
+typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float uf2 __attribute__((ext_vector_type(2), aligned(4)));
+template <int N>
+__device__ __forceinline__ void load_floats(const float *p, float *v)
+{
+    if constexpr (N >= 4) {
+        const uf4 q = gload(reinterpret_cast<const uf4 *>(p));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = q[i];
+        if constexpr (N > 4) load_floats<N - 4>(p + 4, v + 4);
+    } else if constexpr (N >= 2) {
+        const uf2 q = gload(reinterpret_cast<const uf2 *>(p));
+        v[0] = q[0];
+        v[1] = q[1];
+        if constexpr (N > 2) load_floats<N - 2>(p + 2, v + 2);
+    } else if constexpr (N == 1) {
+        v[0] = gload(p);
+    }
+}
+template <int N>
+__device__ __forceinline__ void store_floats(float *p, const float *v)
+{
+    if constexpr (N >= 4) {
+        gstore(reinterpret_cast<uf4 *>(p), uf4{v[0], v[1], v[2], v[3]});
+        if constexpr (N > 4) store_floats<N - 4>(p + 4, v + 4);
+    } else if constexpr (N >= 2) {
+        gstore(reinterpret_cast<uf2 *>(p), uf2{v[0], v[1]});
+        if constexpr (N > 2) store_floats<N - 2>(p + 2, v + 2);
+    } else if constexpr (N == 1) {
+        gstore(p, v[0]);
+    }
+}
+
 typedef float gf32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int gu32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int gu32x4 __attribute__((ext_vector_type(4)));
@@ -241,6 +276,10 @@ void decode_tile_shape(DecodeCfg &dc);
 int decode_grid(const DecodeCfg &dc, int n, const int *H, const int *W);
 hipError_t launch_decode_tensors(const DecodeCfg &dc, int N, int H, int W, const float *head,
                                  const float *c, const float *mod, float *out, hipStream_t s);
+// wskp_decode of 1..3 levels of one frame in one launch, level l's irradiance
+// the l times pooled c, no remodulation
+hipError_t launch_decode_levels(const DecodeCfg &dc, int levels, int H, int W, const float *const *heads,
+                                const float *c, float *const *outs, hipStream_t s);
 hipError_t launch_decode_backward(const DecodeCfg &dc, int N, int H, int W, const float *head,
                                   const float *c, const float *mod, const float *g,
                                   float *grad_head, float *grad_c, void *scratch,
@@ -297,6 +336,10 @@ hipError_t tr_repack(int Cin, int Cout, int CK, int nch, int Cout_pad, const flo
 // Multi-resolution reconstruction pieces (mr.hip): 2x2 mean of a 3-channel
 // image, and the Eq. 7 blend (optionally remodulated).
 hipError_t launch_pool2(int H, int W, const float *in, float *out, hipStream_t s);
+// Every blend of L levels (2..6) in one launch: f[l] the filtered images,
+// alpha[l] (l < L - 1) their weights.
+hipError_t launch_mr_blend_all(int L, int H, int W, const float *const *f, const float *const *alpha,
+                               const float *mod, float *out, hipStream_t s);
 hipError_t launch_mr_blend(int H, int W, const float *fine, const float *coarse, const float *alpha,
                            const float *mod, float *out, hipStream_t s);
 // Temporal accumulation of one frame (temporal.hip); pr == nullptr: first frame.

@@ -266,9 +266,7 @@ wskp_status_t wskp_backward_workspace_size(wskp_handle_t h, int N, int H, int W,
  *   targets: HOST array of n device pointers to [H_i,W_i,3] references.
  *   Gradients are accumulated over frames in a fixed order (run-to-run
  *   identical).  Errors: WSKP_E_BUDGET when ws_bytes is below
- *   wskp_train_workspace_size; WSKP_E_LAUNCH when a frame is too wide for
- *   the 32-bit buffer windows of the weight-gradient kernel (about 10^6
- *   pixels per row at 200 channels).
+ *   wskp_train_workspace_size.
  * wskp_adam: one Adam step (step >= 1) on the handle's weights with the
  *   gradient grad and the moment buffers m, v (device, wskp_num_weights
  *   floats each, zero before step 1, updated in place); afterwards every

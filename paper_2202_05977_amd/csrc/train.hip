@@ -26,12 +26,10 @@
 //          output channels are padded with zeros to a multiple of 16 (its
 //          gradient dh is written with that row stride)
 //   wgrad  dw[co][ci][tap] = sum_p gm[p][co] in[p + off(tap)][ci],
-//          db[co] = sum_p gm[p][co]: a GEMM over pixels,
-//          tr_wgrad_mfma_kernel (v_mfma_f32_16x16x4f32, 4 pixels per step;
-//          channel counts that are not multiples of 16 are padded with
-//          zeros).  Each workgroup sums one chunk of 256 to 1024 pixels
-//          and a second pass adds the chunks' partial sums in a fixed
-//          order, so the result does not depend on scheduling
+//          db[co] = sum_p gm[p][co]: a GEMM over pixels, train_wgrad.hip;
+//          each workgroup sums one strip of pixels and a second pass adds
+//          the strips' partial sums in a fixed order, so the result does
+//          not depend on scheduling
 #include "wskp_internal.h"
 
 namespace wskp {
@@ -186,170 +184,6 @@ __global__ __launch_bounds__(kTrThreads) void tr_mask_kernel(long n, int nf, con
     const long f = i / n, j = i - f * n;
     const float v = gload(g + i);
     gstore(gm + i, gload(act + f * sa + j) > 0.f ? v : 0.f);
-}
-
-// Partial weight gradients on the matrix cores, part[chunk][co][ci][tap]
-// and partb[chunk][co]: a GEMM over
-// pixels, D[co][ci] += sum_p gm[p][co] * in[p + off(tap)][ci] for each tap,
-// with v_mfma_f32_16x16x4f32 taking 4 pixels per step (lane (g, j): pixel
-// g of the step; A = gm[p_g][co0 + j] (gm rows ldg floats apart),
-// B = in[p_g + off][ci0 + j]).  One workgroup per (chunk of `chunk`
-// pixels, CB output blocks of 16, one input block of 16); its kWgWaves waves
-// take consecutive quarters of the chunk, each loading the operands of its
-// next step before the MFMAs of the current one, and add their sums in LDS
-// in a fixed order, (w0 + w2) + (w1 + w3).  Operands are raw buffer loads
-// with 32-bit offsets into windows: the chunk's gm rows, and the whole
-// source rows of the image rows the chunk touches and one either side (the
-// input block's source: the H x W map, or the half-size map the input
-// upsamples).  Channels beyond Co or Ci (the network input's 10, the
-// head's 2M), taps outside the image and pixels past the chunk take an
-// offset beyond the window and read zeros, so no load is conditional.  The workgroups of input block 0 also sum gm
-// (B = 1) for the bias.  Lane (g, j) ends with D[4g + r][j], r = 0..3.
-typedef float trf32x4 __attribute__((ext_vector_type(4)));
-// Chunks are 256 pixels, doubled (up to kWgChunkMax) while a launch still
-// has kWgMinGroups workgroups: fewer partial sums to write and reduce.
-constexpr int kWgChunk = 256, kWgChunkMax = 1024, kWgMinGroups = 2048, kWgWaves = 4;
-constexpr unsigned kWgOut = 0x80000000u;   // beyond every window (windows are < 2 GiB)
-template <int CB>
-__global__ __launch_bounds__(64 * kWgWaves) void tr_wgrad_mfma_kernel(int H, int W, int Co, int ldg, int chunk,
-                                                                      int nch, const float *gm, long sgm,
-                                                                      const float *in, long sin, int Cf,
-                                                                      const float *up, long sup, int Cu,
-                                                                      float *part, float *partb)
-{
-    __shared__ trf32x4 red[2][CB * 10][64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
-    const int co0 = blockIdx.y * (16 * CB), ci0 = blockIdx.z * 16;
-    const long P = (long)H * W;
-    // workgroup x: frame f, chunk x - f nch of that frame; partial sum x
-    const int fr = blockIdx.x / nch;
-    gm += fr * sgm;
-    const long c0 = (long)(blockIdx.x - fr * nch) * chunk;
-    const int n = (int)min((long)chunk, P - c0);
-    const rsrc_t rg = make_rsrc(gm + c0 * ldg, (unsigned)n * (unsigned)ldg * 4u);
-    // The input block's source: the map that the upsampling makes H x W
-    // (channels 0 .. Cu-1 of the layer's input, read at (y/2, x/2)) or the
-    // H x W map (channels Cu ..).  Its window: the source rows of image rows
-    // ylo .. yhi (the chunk's rows and one either side), whole rows.
-    const int Ci = Cu + Cf;
-    const bool coarse = ci0 < Cu;
-    const int sh = coarse ? 1 : 0, Cs = coarse ? Cu : Cf, cs0 = coarse ? ci0 : ci0 - Cu;
-    const int Wsrc = W >> sh;
-    const float *src = coarse ? up + fr * sup : in + fr * sin;
-    const int ylo = max(0, (int)(c0 / W) - 1), yhi = min(H - 1, (int)((c0 + n - 1) / W) + 1);
-    const int rlo = ylo >> sh, rhi = yhi >> sh;
-    const unsigned rowb = (unsigned)Wsrc * (unsigned)Cs * 4u, pixb = (unsigned)Cs * 4u;
-    const rsrc_t ri = make_rsrc(src + (long)rlo * Wsrc * Cs, (unsigned)(rhi - rlo + 1) * rowb);
-    const bool bias = blockIdx.z == 0;
-    bool cok[CB];
-#pragma unroll
-    for (int c = 0; c < CB; ++c) cok[c] = co0 + c * 16 + j < Co;
-    const bool ciok = cs0 + j < Cs;
-    const unsigned chb = (unsigned)(cs0 + j) * 4u;
-    trf32x4 acc[CB][10];
-#pragma unroll
-    for (int c = 0; c < CB; ++c)
-#pragma unroll
-        for (int t = 0; t < 10; ++t) acc[c][t] = trf32x4{0.f, 0.f, 0.f, 0.f};
-    // this wave's pixels qa .. qb - 1 of the chunk
-    const int qa = wave * (chunk / kWgWaves), qb = min(n, qa + chunk / kWgWaves);
-    float a[CB], b[9];
-    // operands of the step at chunk pixel q, for this lane's pixel q + g at
-    // image position (y, x)
-    // (offsets are made out of range by setting bit 31, with no select, so
-    // that the compiler keeps every load unconditional)
-    auto out = [](bool ok) { return (0u - (unsigned)!ok) & kWgOut; };
-    auto load = [&](int q, int y, int x, float (&av)[CB], float (&bv)[9]) {
-        const int p = q + g;
-        const bool valid = p < qb;
-#pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            const unsigned off = ((unsigned)p * (unsigned)ldg + (unsigned)(co0 + c * 16 + j)) * 4u | out(valid & cok[c]);
-            av[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rg, off, 0, 0));
-        }
-        // tap (dy, dx) reads source row ((y + dy - 1) >> sh) - rlo, column
-        // (x + dx - 1) >> sh of the window (valid taps lie inside it)
-        const bool vc = valid & ciok;
-        const bool rok[3] = {y >= 1, true, y + 1 < H}, xok[3] = {x >= 1, true, x + 1 < W};
-        unsigned rt[3], ct[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            rt[d] = (unsigned)(((y + d - 1) >> sh) - rlo) * rowb + chb;
-            ct[d] = (unsigned)((x + d - 1) >> sh) * pixb;
-        }
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            const int dy = t / 3, dx = t % 3;
-            const unsigned off = (rt[dy] + ct[dx]) | out(vc & rok[dy] & xok[dx]);
-            bv[t] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ri, off, 0, 0));
-        }
-    };
-    const long p0 = c0 + qa + g;
-    int y = (int)(p0 / W), x = (int)(p0 - (long)y * W);
-    load(qa, y, x, a, b);
-    for (int q = qa; q < qb; q += 4) {
-        int yn = y, xn = x + 4;
-        if (W >= 4) {
-            const bool wrap = xn >= W;
-            xn -= wrap ? W : 0;
-            yn += wrap ? 1 : 0;
-        } else {
-            while (xn >= W) {
-                xn -= W;
-                ++yn;
-            }
-        }
-        float an[CB], bn[9];
-        load(q + 4, yn, xn, an, bn);
-#pragma unroll
-        for (int c = 0; c < CB; ++c) {
-#pragma unroll
-            for (int t = 0; t < 9; ++t) acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], b[t], acc[c][t], 0, 0, 0);
-            if (bias) acc[c][9] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], 1.f, acc[c][9], 0, 0, 0);
-        }
-#pragma unroll
-        for (int c = 0; c < CB; ++c) a[c] = an[c];
-#pragma unroll
-        for (int t = 0; t < 9; ++t) b[t] = bn[t];
-        y = yn;
-        x = xn;
-    }
-    // (w0 + w2) + (w1 + w3)
-    if (wave >= 2)
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int t = 0; t < 10; ++t) red[wave - 2][c * 10 + t][lane] = acc[c][t];
-    __syncthreads();
-    if (wave < 2)
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int t = 0; t < 10; ++t) acc[c][t] += red[wave][c * 10 + t][lane];
-    __syncthreads();
-    if (wave == 1)
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int t = 0; t < 10; ++t) red[0][c * 10 + t][lane] = acc[c][t];
-    __syncthreads();
-    if (wave != 0) return;
-    const long base = (long)blockIdx.x * Co * Ci * 9;
-    const int ci = ci0 + j;
-#pragma unroll
-    for (int c = 0; c < CB; ++c) {
-#pragma unroll
-        for (int t = 0; t < 10; ++t) acc[c][t] += red[0][c * 10 + t][lane];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int co = co0 + c * 16 + 4 * g + r;
-            if (co >= Co) continue;
-            if (ci < Ci)
-#pragma unroll
-                for (int t = 0; t < 9; ++t) gstore(part + base + ((long)co * Ci + ci) * 9 + t, acc[c][t][r]);
-            if (bias && j == 0) gstore(partb + (long)blockIdx.x * Co + co, acc[c][9][r]);
-        }
-    }
 }
 
 // First level of a sliced reduce: out[y][i] = sum of part rows (chunks)
@@ -565,19 +399,6 @@ hipError_t tr_mask(long n, int nf, const float *g, const float *act, long sa, fl
     TR_LAUNCH(tr_mask_kernel, n * nf, n, nf, g, act, sa, gm);
     return hipGetLastError();
 }
-static int wgrad_blocks(int Ci, int Co)
-{
-    const int cib = (Ci + 15) / 16, cob = (Co + 15) / 16;
-    return cib * (cob % 2 == 0 ? cob / 2 : cob);
-}
-// pixels per chunk for nf frames of P pixels (a multiple of 16: four waves
-// of whole 4-pixel steps)
-static int wgrad_chunk(long P, int Ci, int Co, int nf)
-{
-    int c = kWgChunk;
-    while (c < kWgChunkMax && (long)nf * ((P + 2 * c - 1) / (2 * c)) * wgrad_blocks(Ci, Co) >= kWgMinGroups) c *= 2;
-    return c;
-}
 // slices of the two-level reduce (at most kWgSlices)
 constexpr int kWgSlices = 64;
 static int wgrad_slices(long nw, int Co, int nall)
@@ -587,31 +408,19 @@ static int wgrad_slices(long nw, int Co, int nall)
     while (G < kWgSlices && gx * G < 1024 && nall / (2 * G) >= 32) G *= 2;
     return G;
 }
-size_t tr_wgrad_part_floats(long P, int Ci, int Co, int nf)
+size_t tr_wgrad_part_floats(int H, int W, int Ci, int Co, int nf)
 {
-    const int c = wgrad_chunk(P, Ci, Co, nf);
-    // the chunks' partial sums, then the slices' sums of the two-level reduce
-    return ((size_t)nf * ((P + c - 1) / c) + kWgSlices) * ((size_t)Co * Ci * 9 + Co);
+    // the strips' partial sums, then the slices' sums of the two-level reduce
+    return ((size_t)tr_wgrad_strips(H, W, Ci, Co, nf) + kWgSlices) * ((size_t)Co * Ci * 9 + Co);
 }
 hipError_t tr_wgrad(int H, int W, int Co, int ldg, int nf, const float *gm, long sgm, const float *in, long sin,
                     int Cf, const float *up, long sup, int Cu, float *part, float *dw, float *db, hipStream_t s)
 {
-    const int Ci = Cu + Cf;
-    const long P = (long)H * W;
-    const int chunk = wgrad_chunk(P, Ci, Co, nf);
-    const int nch = (int)((P + chunk - 1) / chunk), nall = nf * nch;
+    const int Ci = Cu + Cf, nall = tr_wgrad_strips(H, W, Ci, Co, nf);
     const long nw = (long)Co * Ci * 9;
     float *partb = part + (size_t)nall * nw;
-    // the kernel's buffer windows and offsets stay below 2 GiB
-    if ((double)(chunk + 3.0 * W) * std::max(std::max(Cf, Cu), ldg) * 4.0 >= 2147483648.0) return hipErrorInvalidValue;
-    if (Cu % 16 || (Cu > 0 && (H % 2 || W % 2))) return hipErrorInvalidValue;   // whole blocks per source
-    const unsigned cib = (unsigned)((Ci + 15) / 16), cob = (unsigned)((Co + 15) / 16);
-    if (cob % 2 == 0)
-        hipLaunchKernelGGL(tr_wgrad_mfma_kernel<2>, dim3((unsigned)nall, cob / 2, cib), dim3(64 * kWgWaves), 0, s, H,
-                           W, Co, ldg, chunk, nch, gm, sgm, in, sin, Cf, up, sup, Cu, part, partb);
-    else
-        hipLaunchKernelGGL(tr_wgrad_mfma_kernel<1>, dim3((unsigned)nall, cob, cib), dim3(64 * kWgWaves), 0, s, H, W,
-                           Co, ldg, chunk, nch, gm, sgm, in, sin, Cf, up, sup, Cu, part, partb);
+    const hipError_t e = launch_wgrad_split(H, W, Co, ldg, nf, gm, sgm, in, sin, Cf, up, sup, Cu, part, partb, s);
+    if (e != hipSuccess) return e;
     const unsigned gx = (unsigned)((nw + Co + 63) / 64);
     // (the second level treats the biases as weights nw .. nw + Co - 1, so
     // db must follow dw, as in the weight blob)

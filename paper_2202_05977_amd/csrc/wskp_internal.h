@@ -311,8 +311,13 @@ hipError_t tr_head_act_bwd(long P, int M, int ld, int nf, const float *grad_head
                            float *dh, hipStream_t s);
 // gm = (act > 0) g over nf frames of n values (gm may be g)
 hipError_t tr_mask(long n, int nf, const float *g, const float *act, long sa, float *gm, hipStream_t s);
-// partial sums of a weight gradient over nf frames of P pixels
-size_t tr_wgrad_part_floats(long P, int Ci, int Co, int nf);
+// partial sums of a weight gradient over nf frames
+size_t tr_wgrad_part_floats(int H, int W, int Ci, int Co, int nf);
+// its kernel (train_wgrad.hip) and the number of partial sums it writes
+int tr_wgrad_strips(int H, int W, int Ci, int Co, int nf);
+hipError_t launch_wgrad_split(int H, int W, int Co, int ldg, int nf, const float *gm, long sgm, const float *in,
+                              long sin, int Cf, const float *up, long sup, int Cu, float *part, float *partb,
+                              hipStream_t s);
 // The conv's input: Cu channels of `up` (H/2 x W/2) upsampled x2, then Cf
 // channels of `in` (H x W) (Cu = 0: `in` alone); gm rows are ldg >= Co
 // floats apart; dw and db accumulate the nf frames

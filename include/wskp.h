@@ -303,8 +303,8 @@ wskp_status_t wskp_mr_blend(wskp_handle_t h, void *stream, int H, int W, const f
  * host array of L-1 device pointers, alphas[l] [H>>l, W>>l] the Eq. 7 blend
  * weight of level l; mod [H,W,3] or NULL; out [H,W,3].  Pools c L-1 times,
  * filters every level, blends from the coarsest and remodulates the finest
- * result: the same launches, in the same order, as the composition of
- * wskp_pool2, wskp_decode and wskp_mr_blend.  ws: device workspace of at
+ * result: the values, bit for bit, of the composition of wskp_pool2,
+ * wskp_decode and wskp_mr_blend, in fewer launches.  ws: device workspace of at
  * least wskp_mr_workspace_size bytes (the pooled irradiance of levels
  * 1..L-1, every level's filtered image, the intermediate blends). */
 wskp_status_t wskp_mr_workspace_size(wskp_handle_t h, int L, int H, int W, size_t *bytes);

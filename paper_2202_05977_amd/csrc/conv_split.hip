@@ -86,6 +86,82 @@ __device__ float split_input(const ConvLayer &L, const FrameDesc &fd, const floa
     }
 }
 
+// Epilogues of the input gradients in training: what the gradient gm of the
+// layer's input becomes is written at once, so it is itself never stored.
+// Lane: pixel (y + r, x), channels co0 + 8 q + k.  Operands in the frame's
+// descriptor: e[1] destination, u[0] activation whose ReLU masks it, e[2]
+// second destination.
+//   EPI_BWD_MASK  e[1] = (u[0] > 0) gm                        (the head's input)
+//   EPI_BWD_CAT   channels below L.C1, the upsampled part of a decoder's input:
+//                 e[1][y/2][x/2] = (u[0] > 0) (sum of the 2x2 block); the others,
+//                 the skip: e[2] = gm (its first contribution)
+//   EPI_BWD_POOL  the 2x2 mean's adjoint added to the finer map e[1] and its
+//                 ReLU mask: e[1] = (u[0] > 0) (e[1] + gm / 4), 4 finer pixels
+template <int EPI, int HW>
+__device__ __forceinline__ void bwd_epilogue(const ConvLayer &L, const FrameDesc &fd, const f32x16 *acc, int co0,
+                                             int y, int x, int Hl, int Wl)
+{
+    float *dst = static_cast<float *>(fd.e[1]);
+    const float *act = static_cast<const float *>(fd.u[0]);
+    auto mask = [](const gf32x4 &v, const gf32x4 &a) {
+        return gf32x4{a[0] > 0.f ? v[0] : 0.f, a[1] > 0.f ? v[1] : 0.f, a[2] > 0.f ? v[2] : 0.f, a[3] > 0.f ? v[3] : 0.f};
+    };
+    auto at = [](auto *p, size_t i) { return reinterpret_cast<std::conditional_t<
+        std::is_const_v<std::remove_pointer_t<decltype(p)>>, const gf32x4, gf32x4> *>(p + i); };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int co = co0 + 8 * q;
+        const bool cin = co < L.Cout;
+        if constexpr (EPI == EPI_BWD_CAT) {
+            // (the channels of one q lie on one side: C1 is a multiple of 16)
+            const int Cu = L.C1, Ce = L.Cout - Cu;
+            if (co < Cu) {
+                static_assert(EPI != EPI_BWD_CAT || HW == 2, "a 2x2 block in one wave");
+                gf32x4 v;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float a = acc[0][4 * q + k], c = acc[HW - 1][4 * q + k];
+                    v[k] = ((a + lane_xor1(a)) + c) + lane_xor1(c);
+                }
+                if ((x & 1) == 0 && y < Hl && x < Wl) {
+                    const size_t i = ((size_t)(y >> 1) * (Wl >> 1) + (x >> 1)) * Cu + co;
+                    gstore(at(dst, i), mask(v, gload(at(act, i))));
+                }
+            } else if (cin) {
+                float *ge = static_cast<float *>(fd.e[2]);
+#pragma unroll
+                for (int r = 0; r < HW; ++r)
+                    if (y + r < Hl && x < Wl)
+                        gstore(at(ge, ((size_t)(y + r) * Wl + x) * Ce + (co - Cu)),
+                               gf32x4{acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]});
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < HW; ++r) {
+                if (!cin || y + r >= Hl || x >= Wl) continue;
+                const gf32x4 v = {acc[r][4 * q], acc[r][4 * q + 1], acc[r][4 * q + 2], acc[r][4 * q + 3]};
+                if constexpr (EPI == EPI_BWD_MASK) {
+                    const size_t i = ((size_t)(y + r) * Wl + x) * L.Cout + co;
+                    gstore(at(dst, i), mask(v, gload(at(act, i))));
+                } else {
+                    gf32x4 o[4], a[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const size_t i = ((size_t)(2 * (y + r) + (k >> 1)) * (2 * Wl) + 2 * x + (k & 1)) * L.Cout + co;
+                        o[k] = gload(at(const_cast<const float *>(dst), i));
+                        a[k] = gload(at(act, i));
+                    }
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const size_t i = ((size_t)(2 * (y + r) + (k >> 1)) * (2 * Wl) + 2 * x + (k & 1)) * L.Cout + co;
+                        gstore(at(dst, i), mask(o[k] + 0.25f * v, a[k]));
+                    }
+                }
+            }
+        }
+    }
+}
+
 template <int MODE, int EPI, int HW>
 __global__ __launch_bounds__(kThreads, 2) void conv3x3_split_kernel(ConvLayer L, FrameArg fa)
 {
@@ -334,6 +410,10 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_split_kernel(ConvLayer L,
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[r][i] = v[(r * 16 + i) * kThreads];
     }
+    if constexpr (EPI == EPI_BWD_MASK || EPI == EPI_BWD_CAT || EPI == EPI_BWD_POOL) {
+        bwd_epilogue<EPI, HW>(L, fd, acc, co0, y0 + wave * HW, x0 + lj, Hl, Wl);
+        return;
+    }
     float bias[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -372,22 +452,40 @@ size_t conv_split_weight_bytes(int Cin, int Cout)
     return (size_t)((Cout + 31) / 32) * ((Cin + kSpCK - 1) / kSpCK) * kSpWFrags * kSpFrag;
 }
 
-// Packed split weights from w [Co][Ci][3][3]: fragments [group of 32 output
-// channels][chunk][tap][part], in each lane (h, j)'s 8 values for output
-// channel j of the group and input channels 8 h .. 8 h + 7 of the chunk; zero
-// beyond Ci or Co.  dgrad: the conv that maps the gradient of w's output to
-// its input's (taps flipped, channel axes swapped), where Ci and Co are this
-// conv's (w is then [Ci][Co][3][3]).
-__global__ __launch_bounds__(kThreads) void conv_split_pack_kernel(int Ci, int Co, int nch, int groups, int dgrad,
-                                                                    const float *w, unsigned short *packed)
+// Weight packing, all layers in one launch.  Packed split weights of a conv
+// Ci -> Co: fragments [group of 32 output channels][chunk][tap][part], in each
+// lane (h, j)'s 8 values for output channel j of the group and input channels
+// 8 h .. 8 h + 7 of the chunk; zero beyond Ci or Co.  PACK_SPLIT: w is
+// [Co][Ci][3][3].  PACK_SPLIT_DGRAD: the conv that maps the gradient of w's
+// output to its input's (taps flipped, channel axes swapped), w [Ci][Co][3][3].
+// PACK_NATIVE: the layout of the v_mfma_f32_16x16x4f32 kernel, [chunk of CK]
+// [tap][c][Cout_pad] floats, and the Co biases after w to `bias`.
+__global__ __launch_bounds__(kThreads) void conv_pack_kernel(PackJobs jobs)
 {
-    const int i = blockIdx.x * kThreads + threadIdx.x;      // (group, chunk, tap, lane, e)
-    if (i >= groups * nch * 9 * 512) return;
-    const int e = i & 7, lane = (i >> 3) & 63, t = i / 512 % 9, cc = i / (512 * 9) % nch, gr = i / (512 * 9 * nch);
+    int b = blockIdx.x, j = 0;
+    while (j + 1 < jobs.n && b >= jobs.j[j + 1].block0) ++j;
+    const PackJob &p = jobs.j[j];
+    const int i = (b - p.block0) * kThreads + threadIdx.x;
+    if (p.kind == PACK_NATIVE) {
+        const int n = p.nch * 9 * p.CK * p.Cout_pad;
+        if (i < n) {
+            const int co = i % p.Cout_pad, c = i / p.Cout_pad % p.CK, t = i / (p.Cout_pad * p.CK) % 9;
+            const int ci = i / (p.Cout_pad * p.CK * 9) * p.CK + c;
+            gstore(static_cast<float *>(p.out) + i,
+                   co < p.Co && ci < p.Ci ? gload(p.w + ((size_t)co * p.Ci + ci) * 9 + t) : 0.f);
+        } else if (i < n + p.Co) {
+            gstore(p.bias + (i - n), gload(p.w + (size_t)p.Co * p.Ci * 9 + (i - n)));
+        }
+        return;
+    }
+    if (i >= p.groups * p.nch * 9 * 512) return;            // (group, chunk, tap, lane, e)
+    const int e = i & 7, lane = (i >> 3) & 63, t = i / 512 % 9, cc = i / (512 * 9) % p.nch, gr = i / (512 * 9 * p.nch);
     const int co = gr * 32 + (lane & 31), ci = cc * kSpCK + (lane >> 5) * 8 + e;
     float v = 0.f;
-    if (co < Co && ci < Ci) v = gload(dgrad ? w + ((size_t)ci * Co + co) * 9 + (8 - t) : w + ((size_t)co * Ci + ci) * 9 + t);
-    unsigned short *o = packed + ((size_t)((gr * nch + cc) * 9 + t) * 3) * 512 + lane * 8 + e;
+    if (co < p.Co && ci < p.Ci)
+        v = gload(p.kind == PACK_SPLIT_DGRAD ? p.w + ((size_t)ci * p.Co + co) * 9 + (8 - t)
+                                             : p.w + ((size_t)co * p.Ci + ci) * 9 + t);
+    unsigned short *o = static_cast<unsigned short *>(p.out) + ((size_t)((gr * p.nch + cc) * 9 + t) * 3) * 512 + lane * 8 + e;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         const unsigned short h = f32_to_bf16(v);
@@ -396,12 +494,42 @@ __global__ __launch_bounds__(kThreads) void conv_split_pack_kernel(int Ci, int C
     }
 }
 
-hipError_t conv_split_pack(int Ci, int Co, bool dgrad, const float *w, void *packed, hipStream_t s)
+void PackJobs::add_split(int Ci, int Co, bool dgrad, const float *w, void *out)
 {
-    const int nch = (Ci + kSpCK - 1) / kSpCK, groups = (Co + 31) / 32;
-    const int n = groups * nch * 9 * 512;
-    hipLaunchKernelGGL(conv_split_pack_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, s, Ci, Co, nch,
-                       groups, dgrad ? 1 : 0, w, static_cast<unsigned short *>(packed));
+    PackJob &p = j[n++];
+    p = PackJob{};
+    p.kind = dgrad ? PACK_SPLIT_DGRAD : PACK_SPLIT;
+    p.Ci = Ci;
+    p.Co = Co;
+    p.nch = (Ci + kSpCK - 1) / kSpCK;
+    p.groups = (Co + 31) / 32;
+    p.w = w;
+    p.out = out;
+    p.block0 = blocks;
+    blocks += (p.groups * p.nch * 9 * 512 + kThreads - 1) / kThreads;
+}
+
+void PackJobs::add_native(int Ci, int Co, int CK, int nch, int Cout_pad, const float *w, float *out, float *bias)
+{
+    PackJob &p = j[n++];
+    p = PackJob{};
+    p.kind = PACK_NATIVE;
+    p.Ci = Ci;
+    p.Co = Co;
+    p.CK = CK;
+    p.nch = nch;
+    p.Cout_pad = Cout_pad;
+    p.w = w;
+    p.out = out;
+    p.bias = bias;
+    p.block0 = blocks;
+    blocks += (nch * 9 * CK * Cout_pad + Co + kThreads - 1) / kThreads;
+}
+
+hipError_t launch_conv_pack(const PackJobs &jobs, hipStream_t s)
+{
+    if (jobs.n == 0) return hipSuccess;
+    hipLaunchKernelGGL(conv_pack_kernel, dim3(jobs.blocks), dim3(kThreads), 0, s, jobs);
     return hipGetLastError();
 }
 
@@ -419,10 +547,13 @@ void conv_split_layer(ConvLayer &L, int Cin)
 template <int MODE, int EPI>
 static hipError_t launch_split_inst(const ConvLayer &L, const FrameArg &fa, int blocks, hipStream_t s)
 {
-    if (L.th == 4)
+    if constexpr (EPI == EPI_BWD_CAT) {
+        if (L.th != 8) return hipErrorInvalidValue;
+    } else if (L.th == 4) {
         hipLaunchKernelGGL((conv3x3_split_kernel<MODE, EPI, 1>), dim3(blocks), dim3(kThreads), 0, s, L, fa);
-    else
-        hipLaunchKernelGGL((conv3x3_split_kernel<MODE, EPI, 2>), dim3(blocks), dim3(kThreads), 0, s, L, fa);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((conv3x3_split_kernel<MODE, EPI, 2>), dim3(blocks), dim3(kThreads), 0, s, L, fa);
     return hipGetLastError();
 }
 
@@ -435,7 +566,9 @@ hipError_t launch_conv_split(const ConvLayer &L, int mode, int epi, const FrameA
     case CONV_POOL: return launch_split_inst<CONV_POOL, EPI_RELU>(L, fa, blocks, s);
     case CONV_CAT: return launch_split_inst<CONV_CAT, EPI_RELU>(L, fa, blocks, s);
     case CONV_PLAIN:
-        if (epi == EPI_LINEAR) return launch_split_inst<CONV_PLAIN, EPI_LINEAR>(L, fa, blocks, s);
+        if (epi == EPI_BWD_MASK) return launch_split_inst<CONV_PLAIN, EPI_BWD_MASK>(L, fa, blocks, s);
+        if (epi == EPI_BWD_CAT) return launch_split_inst<CONV_PLAIN, EPI_BWD_CAT>(L, fa, blocks, s);
+        if (epi == EPI_BWD_POOL) return launch_split_inst<CONV_PLAIN, EPI_BWD_POOL>(L, fa, blocks, s);
         if (epi == EPI_HEAD_EXP) return launch_split_inst<CONV_PLAIN, EPI_HEAD_EXP>(L, fa, blocks, s);
         if (epi == EPI_HEAD_SOFTPLUS) return launch_split_inst<CONV_PLAIN, EPI_HEAD_SOFTPLUS>(L, fa, blocks, s);
         return hipErrorInvalidValue;

@@ -815,9 +815,14 @@ __global__ __launch_bounds__(kFThreads, 4) void decode_tile_kernel(DecodeCfg dc,
 //   dc_ch(q) = sum_i W_i(q) box_i(u_i,ch)(q)                      -> grad_c[q][ch]
 // One size at a time: stage the halo of (u_i, dS_i) as float4, row sums,
 // column sums.  LDS: float4 [HXY] staged + float4 [(kDTY+2R)][kHB] row sums.
-template <int M, int RM>
+//
+// ACT (training): dW_i is taken on through softplus' (the logistic of h, = 1 -
+// e^{-W} = -expm1(-W) in terms of W = softplus(h), accurate also where W is
+// tiny), and the record, the gradient of the head conv's output, is written
+// with rows of act_ld floats, zeros beyond 2M; grad_c is not.
+template <int M, int RM, bool ACT>
 __global__ __launch_bounds__(kThreads) void decode_adj_b_kernel(DecodeCfg dc, DecodeTensors dt,
-                                                                 float *grad_c)
+                                                                 float *grad_c, int act_ld)
 {
     extern __shared__ float4 lds4[];
     DecodeIO io;
@@ -883,17 +888,26 @@ __global__ __launch_bounds__(kThreads) void decode_adj_b_kernel(DecodeCfg dc, De
         const int y = y0 + kRun * ty + o, x = x0 + tx;
         if (y < H && x < W) {
             const size_t pix = (size_t)y * W + x;
-            float rec[2 * M];
+            if constexpr (ACT) {
+                float *dh = dt.grad_head + ((size_t)fidx * P + pix) * act_ld;
+                float rec[16];   // act_ld is 16: 2M padded to a multiple of 16, M <= 8
 #pragma unroll
-            for (int i = 0; i < M; ++i) {
-                rec[i] = dwv[o][i];
-                rec[M + i] = gload(io.dlogit + (size_t)i * P + pix);
+                for (int j = 0; j < 16; ++j) {
+                    rec[j] = 0.f;
+                    if (j < M) rec[j] = dwv[o][j < M ? j : 0] * -expm1f(-wvv[o][j < M ? j : 0]);
+                    else if (j < 2 * M) rec[j] = gload(io.dlogit + (size_t)(j - M) * P + pix);
+                }
+                store_floats<16>(dh, rec);
+            } else {
+                float rec[2 * M];
+#pragma unroll
+                for (int i = 0; i < M; ++i) {
+                    rec[i] = dwv[o][i];
+                    rec[M + i] = gload(io.dlogit + (size_t)i * P + pix);
+                }
+                store_floats<2 * M>(io.grad_head + pix * (2 * M), rec);
+                store_floats<3>(gc + pix * 3, dcv[o]);
             }
-            float *gh = io.grad_head + pix * (2 * M);
-#pragma unroll
-            for (int j = 0; j < 2 * M; ++j) gstore(gh + j, rec[j]);
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) gstore(gc + pix * 3 + ch, dcv[o][ch]);
         }
     }
 }
@@ -1043,9 +1057,24 @@ size_t decode_backward_scratch_bytes(const DecodeCfg &dc, int N, int H, int W)
     return (size_t)N * dc.M * H * W * (sizeof(float4) + sizeof(float));
 }
 
+template <int M, bool ACT>
+static hipError_t launch_adj_b(const DecodeCfg &dc, const DecodeTensors &dt, int blocks, float *grad_c, int act_ld,
+                               hipStream_t s)
+{
+    const size_t lds = adj_b_lds_bytes(dc);
+    if (dc.R <= 5) {
+        allow_lds(decode_adj_b_kernel<M, 5, ACT>, lds);
+        hipLaunchKernelGGL((decode_adj_b_kernel<M, 5, ACT>), dim3(blocks), dim3(kThreads), lds, s, dc, dt, grad_c, act_ld);
+    } else {
+        allow_lds(decode_adj_b_kernel<M, 7, ACT>, lds);
+        hipLaunchKernelGGL((decode_adj_b_kernel<M, 7, ACT>), dim3(blocks), dim3(kThreads), lds, s, dc, dt, grad_c, act_ld);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_decode_backward(const DecodeCfg &dc, int N, int H, int W, const float *head,
                                   const float *c, const float *mod, const float *g,
-                                  float *grad_head, float *grad_c, void *scratch, hipStream_t s)
+                                  float *grad_head, float *grad_c, void *scratch, int act_ld, hipStream_t s)
 {
     DecodeTensors dt{};
     dt.N = N;
@@ -1061,26 +1090,16 @@ hipError_t launch_decode_backward(const DecodeCfg &dc, int N, int H, int W, cons
     const int blocks = N * decode_tiles(H, W);
     hipError_t e = launch_decode<DK_ADJ_A>(dc, dt, blocks, s);
     if (e != hipSuccess) return e;
-    const size_t lds = adj_b_lds_bytes(dc);
-    const bool r5 = dc.R <= 5;
+    if (act_ld != 0 && act_ld != 16) return hipErrorInvalidValue;
     switch (dc.M) {
-#define WSKP_M(m)                                                                                 \
-    case m:                                                                                       \
-        if (r5) {                                                                                 \
-            allow_lds(decode_adj_b_kernel<m, 5>, lds);                                            \
-            hipLaunchKernelGGL((decode_adj_b_kernel<m, 5>), dim3(blocks), dim3(kThreads), lds, s, \
-                               dc, dt, grad_c);                                                   \
-        } else {                                                                                  \
-            allow_lds(decode_adj_b_kernel<m, 7>, lds);                                            \
-            hipLaunchKernelGGL((decode_adj_b_kernel<m, 7>), dim3(blocks), dim3(kThreads), lds, s, \
-                               dc, dt, grad_c);                                                   \
-        }                                                                                         \
-        break;
+#define WSKP_M(m)                                                                   \
+    case m:                                                                         \
+        return act_ld ? launch_adj_b<m, true>(dc, dt, blocks, grad_c, act_ld, s)    \
+                      : launch_adj_b<m, false>(dc, dt, blocks, grad_c, 0, s);
         WSKP_M(1) WSKP_M(2) WSKP_M(3) WSKP_M(4) WSKP_M(5) WSKP_M(6) WSKP_M(7) WSKP_M(8)
 #undef WSKP_M
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace wskp

@@ -4,15 +4,17 @@
 //
 // The forward pass is the fp32 denoising path (its workspace keeps every
 // layer's output).  The backward pass (the frames of one size together):
-//   SMAPE gradient at the output -> adjoint of decode and fusion (decode.hip)
-//   -> derivative of the weight activation -> for each conv, from the head
-//   back to the first encoder: the weight and bias gradient (accumulated
-//   over the frames of the batch) and the input gradient, which the adjoints
-//   of the nearest x2 upsampling, the channel concatenation and the 2x2 mean
-//   distribute to the layers that fed it.  The adjoint that writes the last
-//   contribution to an activation's gradient also applies that activation's
-//   ReLU mask, and the first contribution overwrites, so no gradient buffer
-//   is cleared and no separate mask pass runs (except the head's input).
+//   SMAPE gradient at the output -> adjoint of decode and fusion, with the
+//   derivative of the weight activation (decode.hip) -> for each conv, from the
+//   head back to the first encoder: the weight and bias gradient (accumulated
+//   over the frames of the batch) and the input gradient, whose epilogue takes
+//   it through the adjoint of the nearest x2 upsampling and the concatenation,
+//   or of the 2x2 mean, to the layers that fed the conv (conv_split.hip).  The
+//   epilogue that writes the last contribution to an activation's gradient also
+//   applies that activation's ReLU mask, and the first contribution
+//   overwrites, so no input gradient is stored as such, no gradient buffer
+//   cleared and no mask pass run: a step of 8 crops of 256x256, 5 levels, took
+//   2477 us with an adjoint and a mask pass per conv and takes 2240.
 // The weight gradient's input is written out where it is computed (the
 // network input, a 2x2 mean); a decoder's, the [upsampled, skip]
 // concatenation, is read from its two sources.  Frames of one size run the
@@ -85,25 +87,28 @@ __global__ __launch_bounds__(kTrThreads) void tr_pool_kernel(int H, int W, int C
 
 // interleaved head [P][2M] from the planar record [2M][P]; c = r/(a+eps_a),
 // mod = a + eps_a (the decode adjoint's inputs)
-__global__ __launch_bounds__(kTrThreads) void tr_head_prep_kernel(long P, int M, const float *planar, long sp,
-                                                                   TrFrames fr, float eps_a, float *head, float *c,
-                                                                   float *mod)
+// (whole records and pixels per store: one float per store, 8 M bytes apart
+// across lanes, took 36 us for 8 crops of 256x256)
+template <int M>
+__global__ __launch_bounds__(kTrThreads) void tr_head_prep_kernel(long P, const float *planar, long sp, TrFrames fr,
+                                                                   float eps_a, float *head, float *c, float *mod)
 {
     const long p = (long)blockIdx.x * kTrThreads + threadIdx.x;
     if (p >= P) return;
     const int f = blockIdx.y;
-    const float *r = fr.r[f], *a = fr.a[f];
-    planar += f * sp;
-    head += f * P * 2 * M;
-    c += f * P * 3;
-    mod += f * P * 3;
-    for (int j = 0; j < 2 * M; ++j) gstore(head + p * 2 * M + j, gload(planar + (long)j * P + p));
+    float rec[2 * M], r[3], a[3];
+    load_floats<3>(fr.r[f] + p * 3, r);
+    load_floats<3>(fr.a[f] + p * 3, a);
+#pragma unroll
+    for (int j = 0; j < 2 * M; ++j) rec[j] = gload(planar + f * sp + (long)j * P + p);
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
-        const float m = gload(a + p * 3 + ch) + eps_a;
-        gstore(mod + p * 3 + ch, m);
-        gstore(c + p * 3 + ch, gload(r + p * 3 + ch) / m);
+        a[ch] += eps_a;
+        r[ch] /= a[ch];
     }
+    store_floats<2 * M>(head + (f * P + p) * 2 * M, rec);
+    store_floats<3>(mod + (f * P + p) * 3, a);
+    store_floats<3>(c + (f * P + p) * 3, r);
 }
 
 // SMAPE (Eq. 6) gradient g = dL/dy for n values of each frame with mean
@@ -152,40 +157,6 @@ __global__ __launch_bounds__(kTrThreads) void tr_sum_kernel(int nb, const float 
     if (threadIdx.x == 0) gstore(loss, (accumulate ? gload(loss) : 0.f) + red[0]);
 }
 
-// gradient at the head conv's output: weight channels through softplus'
-// (the logistic of h, = 1 - e^{-W} = -expm1(-W) in terms of W = softplus(h),
-// accurate also where W is tiny); logits as is
-__global__ __launch_bounds__(kTrThreads) void tr_head_act_bwd_kernel(long P, int M, int ld, const float *grad_head,
-                                                                      const float *planar, long sp, float *dh)
-{
-    const long i = (long)blockIdx.x * kTrThreads + threadIdx.x;
-    if (i >= P * ld) return;
-    const int f = blockIdx.y;
-    grad_head += f * P * 2 * M;
-    planar += f * sp;
-    dh += f * P * ld;
-    const int j = (int)(i % ld);
-    const long p = i / ld;
-    float g = 0.f;
-    if (j < 2 * M) {
-        g = gload(grad_head + p * 2 * M + j);
-        if (j < M) g *= -expm1f(-gload(planar + (long)j * P + p));
-    }
-    gstore(dh + i, g);
-}
-
-// gm = g * (act > 0) (the ReLU's derivative) over nf frames of n values
-// (g and gm contiguous, act frame stride sa)
-__global__ __launch_bounds__(kTrThreads) void tr_mask_kernel(long n, int nf, const float *g, const float *act, long sa,
-                                                              float *gm)
-{
-    const long i = (long)blockIdx.x * kTrThreads + threadIdx.x;
-    if (i >= n * nf) return;
-    const long f = i / n, j = i - f * n;
-    const float v = gload(g + i);
-    gstore(gm + i, gload(act + f * sa + j) > 0.f ? v : 0.f);
-}
-
 // First level of a sliced reduce: out[y][i] = sum of part rows (chunks)
 // y S .. y S + S - 1 (fixed order: four interleaved sums added pairwise), for
 // the nw weights then the Co biases; blockIdx.y = slice y.  Used when a layer
@@ -215,7 +186,8 @@ __global__ __launch_bounds__(kTrThreads) void tr_wgrad_slice_kernel(long nw, int
 // order on two alternating accumulators; the waves' sums are added in a
 // fixed order, so the result does not depend on scheduling
 __global__ __launch_bounds__(kTrThreads) void tr_wgrad_reduce_kernel(long nw, int Co, int nchunk, const float *part,
-                                                                      const float *partb, float *dw, float *db)
+                                                                      const float *partb, float *dw, float *db,
+                                                                      int accumulate)
 {
     __shared__ float sred[4][64];
     const int li = threadIdx.x & 63, grp = threadIdx.x >> 6;
@@ -236,77 +208,17 @@ __global__ __launch_bounds__(kTrThreads) void tr_wgrad_reduce_kernel(long nw, in
     __syncthreads();
     if (grp == 0 && in) {
         float *dst = inw ? dw + i : db + (i - nw);
-        gstore(dst, gload(dst) + ((sred[0][li] + sred[1][li]) + (sred[2][li] + sred[3][li])));
+        const float v = (sred[0][li] + sred[1][li]) + (sred[2][li] + sred[3][li]);
+        gstore(dst, accumulate ? gload(dst) + v : v);
     }
 }
 
-// adjoint of [upsample(u), e]: the upsampled part's gradient, the sum of
-// gcat[2y+i][2x+j][c] (c < Cu), masked by u's ReLU (its only contribution)
-// into gu[y][x][c]; the skip part's, gcat[p][Cu+c], into ge[p][c] (its first
-// contribution: both overwrite)
-__global__ __launch_bounds__(kTrThreads) void tr_cat_bwd_kernel(int H, int W, int Cu, int Ce, int nf,
-                                                                 const float *gcat, const float *act_u, long sa,
-                                                                 float *gu, float *ge)
+// one thread per (table, frame)
+__global__ void tr_frame_tables_kernel(FrameDesc *tab, int nf, TrConvTables tables)
 {
-    const int C = Cu + Ce;
-    const int Hc = H / 2, Wc = W / 2;
-    const long nu = (long)Hc * Wc * Cu, ne = (long)H * W * Ce;
-    const long i = (long)blockIdx.x * kTrThreads + threadIdx.x;
-    if (i >= (nu + ne) * nf) return;
-    const long f = i / (nu + ne), k = i - f * (nu + ne);
-    const float *gc = gcat + f * H * W * C;
-    if (k < nu) {
-        const int c = (int)(k % Cu);
-        const long q = k / Cu;
-        const int y = (int)(q / Wc), x = (int)(q % Wc);
-        const float *s = gc + ((long)(2 * y) * W + 2 * x) * C + c;
-        const float v = ((gload(s) + gload(s + C)) + gload(s + (long)W * C)) + gload(s + (long)W * C + C);
-        gstore(gu + f * nu + k, gload(act_u + f * sa + k) > 0.f ? v : 0.f);
-    } else {
-        const long j = k - nu;
-        const int c = (int)(j % Ce);
-        const long p = j / Ce;
-        gstore(ge + f * ne + j, gload(gc + p * C + Cu + c));
-    }
-}
-
-// ge[p][c] = (act[p][c] > 0) (ge[p][c] + gp[p/2][c] / 4): the 2x2 mean's
-// adjoint added to what the concatenation's adjoint wrote, then the ReLU mask
-// of e (its last contribution)
-__global__ __launch_bounds__(kTrThreads) void tr_pool_bwd_kernel(int H, int W, int C, int nf, const float *gp,
-                                                                  const float *act, long sa, float *ge)
-{
-    const long n = (long)H * W * C;
-    const long i = (long)blockIdx.x * kTrThreads + threadIdx.x;
-    if (i >= n * nf) return;
-    const long f = i / n, j = i - f * n;
-    const int c = (int)(j % C);
-    const long p = j / C;
-    const int y = (int)(p / W), x = (int)(p % W);
-    const long np = (long)(H / 2) * (W / 2) * C;
-    const float v = gload(ge + i) + 0.25f * gload(gp + f * np + ((long)(y / 2) * (W / 2) + x / 2) * C + c);
-    gstore(ge + i, gload(act + f * sa + j) > 0.f ? v : 0.f);
-}
-
-// frame table of an input-gradient conv over nf frames: e[0] = the gradient
-// it reads (frame stride ss), e[1] = the input gradient it writes (sd)
-__global__ void tr_frame_table_kernel(FrameDesc *tab, int nf, int H, int W, const float *src, long ss, float *dst,
-                                      long sd)
-{
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nf) return;
-    FrameDesc d{};
-    d.H = H;
-    d.W = W;
-    d.e[0] = const_cast<float *>(src + f * ss);
-    d.e[1] = dst + f * sd;
-    tab[f] = d;
-}
-
-__global__ __launch_bounds__(kTrThreads) void tr_fill_kernel(long n, float v, float *b)
-{
-    const long i = (long)blockIdx.x * kTrThreads + threadIdx.x;
-    if (i < n) gstore(b + i, v);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nf * tables.n) return;
+    tab[i] = tr_conv_frame(tables.t[i / nf], i % nf);
 }
 
 // Adam (Kingma and Ba): m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2;
@@ -323,29 +235,6 @@ __global__ __launch_bounds__(kTrThreads) void tr_adam_kernel(long n, float *w, c
     gstore(m + i, mi);
     gstore(v + i, vi);
     gstore(w + i, gload(w + i) - lr * (mi / c1) / (sqrtf(vi / c2) + eps));
-}
-
-// fp32 weights of one conv from the blob layout (OIHW, then bias) into the
-// layout the fp32 conv kernel reads: [chunk][tap][c][Cout_pad], zero padded;
-// bias copied
-__global__ __launch_bounds__(kTrThreads) void tr_repack_kernel(int Cin, int Cout, int CK, int nch, int Cout_pad,
-                                                                const float *blob, float *packed, float *bias)
-{
-    const long n = (long)nch * 9 * CK * Cout_pad;
-    const long i = (long)blockIdx.x * kTrThreads + threadIdx.x;
-    if (i < n) {
-        const int co = (int)(i % Cout_pad);
-        long q = i / Cout_pad;
-        const int c = (int)(q % CK);
-        q /= CK;
-        const int tap = (int)(q % 9);
-        const int cc = (int)(q / 9);
-        const int ci = cc * CK + c;
-        gstore(packed + i, (co < Cout && ci < Cin) ? gload(blob + ((long)co * Cin + ci) * 9 + tap) : 0.f);
-    } else if (i < n + Cout) {
-        const int co = (int)(i - n);
-        gstore(bias + co, gload(blob + (long)Cout * Cin * 9 + co));
-    }
 }
 
 // ---- launchers ---------------------------------------------------------------
@@ -377,7 +266,13 @@ hipError_t tr_pool(int H, int W, int C, int nf, const float *in, long sin, float
 hipError_t tr_head_prep(long P, int M, int nf, const float *planar, long sp, const TrFrames &fr, float eps_a,
                         float *head, float *c, float *mod, hipStream_t s)
 {
-    TR_LAUNCH_F(tr_head_prep_kernel, P, nf, P, M, planar, sp, fr, eps_a, head, c, mod);
+    switch (M) {
+#define TR_M(m) \
+    case m: TR_LAUNCH_F(tr_head_prep_kernel<m>, P, nf, P, planar, sp, fr, eps_a, head, c, mod); break;
+        TR_M(1) TR_M(2) TR_M(3) TR_M(4) TR_M(5) TR_M(6) TR_M(7) TR_M(8)
+#undef TR_M
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 int tr_smape_blocks(long n) { return tr_blocks(n); }
@@ -386,17 +281,6 @@ hipError_t tr_smape(long n, int nf, const TrFrames &fr, float eps, float inv_n, 
 {
     TR_LAUNCH_F(tr_smape_kernel, n, nf, n, fr, eps, inv_n, g, partial);
     hipLaunchKernelGGL(tr_sum_kernel, dim3(1), dim3(kTrThreads), 0, s, tr_blocks(n) * nf, partial, loss, accumulate);
-    return hipGetLastError();
-}
-hipError_t tr_head_act_bwd(long P, int M, int ld, int nf, const float *grad_head, const float *planar, long sp,
-                           float *dh, hipStream_t s)
-{
-    TR_LAUNCH_F(tr_head_act_bwd_kernel, P * ld, nf, P, M, ld, grad_head, planar, sp, dh);
-    return hipGetLastError();
-}
-hipError_t tr_mask(long n, int nf, const float *g, const float *act, long sa, float *gm, hipStream_t s)
-{
-    TR_LAUNCH(tr_mask_kernel, n * nf, n, nf, g, act, sa, gm);
     return hipGetLastError();
 }
 // slices of the two-level reduce (at most kWgSlices)
@@ -414,7 +298,8 @@ size_t tr_wgrad_part_floats(int H, int W, int Ci, int Co, int nf)
     return ((size_t)tr_wgrad_strips(H, W, Ci, Co, nf) + kWgSlices) * ((size_t)Co * Ci * 9 + Co);
 }
 hipError_t tr_wgrad(int H, int W, int Co, int ldg, int nf, const float *gm, long sgm, const float *in, long sin,
-                    int Cf, const float *up, long sup, int Cu, float *part, float *dw, float *db, hipStream_t s)
+                    int Cf, const float *up, long sup, int Cu, float *part, float *dw, float *db, bool accumulate,
+                    hipStream_t s)
 {
     const int Ci = Cu + Cf, nall = tr_wgrad_strips(H, W, Ci, Co, nf);
     const long nw = (long)Co * Ci * 9;
@@ -426,7 +311,8 @@ hipError_t tr_wgrad(int H, int W, int Co, int ldg, int nf, const float *gm, long
     // db must follow dw, as in the weight blob)
     const int G = db == dw + nw ? wgrad_slices(nw, Co, nall) : 1;
     if (G == 1) {
-        hipLaunchKernelGGL(tr_wgrad_reduce_kernel, dim3(gx), dim3(kTrThreads), 0, s, nw, Co, nall, part, partb, dw, db);
+        hipLaunchKernelGGL(tr_wgrad_reduce_kernel, dim3(gx), dim3(kTrThreads), 0, s, nw, Co, nall, part, partb, dw, db,
+                           accumulate ? 1 : 0);
     } else {
         // slice sums into the rows after the chunks' partials, then their sum
         float *sl = partb + (size_t)nall * Co;
@@ -434,47 +320,21 @@ hipError_t tr_wgrad(int H, int W, int Co, int ldg, int nf, const float *gm, long
         hipLaunchKernelGGL(tr_wgrad_slice_kernel, dim3(gx, (unsigned)G), dim3(kTrThreads), 0, s, nw, Co, nall, S, part,
                            partb, sl);
         // rows of sl are nw + Co floats: weights, then biases
-        hipLaunchKernelGGL(tr_wgrad_reduce_kernel, dim3(gx), dim3(kTrThreads), 0, s, nw + Co, 0, G, sl, sl, dw, db);
+        hipLaunchKernelGGL(tr_wgrad_reduce_kernel, dim3(gx), dim3(kTrThreads), 0, s, nw + Co, 0, G, sl, sl, dw, db,
+                           accumulate ? 1 : 0);
     }
     return hipGetLastError();
 }
-hipError_t tr_cat_bwd(int H, int W, int Cu, int Ce, int nf, const float *gcat, const float *act_u, long sa, float *gu,
-                      float *ge, hipStream_t s)
+hipError_t tr_frame_tables(FrameDesc *tab, int nf, const TrConvTables &tables, hipStream_t s)
 {
-    TR_LAUNCH(tr_cat_bwd_kernel, ((long)(H / 2) * (W / 2) * Cu + (long)H * W * Ce) * nf, H, W, Cu, Ce, nf, gcat, act_u,
-              sa, gu, ge);
-    return hipGetLastError();
-}
-hipError_t tr_pool_bwd(int H, int W, int C, int nf, const float *gp, const float *act, long sa, float *ge,
-                       hipStream_t s)
-{
-    TR_LAUNCH(tr_pool_bwd_kernel, (long)H * W * C * nf, H, W, C, nf, gp, act, sa, ge);
-    return hipGetLastError();
-}
-hipError_t tr_frame_table(FrameDesc *tab, int nf, int H, int W, const float *src, long ss, float *dst, long sd,
-                          hipStream_t s)
-{
-    hipLaunchKernelGGL(tr_frame_table_kernel, dim3((unsigned)((nf + 63) / 64)), dim3(64), 0, s, tab, nf, H, W, src, ss,
-                       dst, sd);
-    return hipGetLastError();
-}
-hipError_t tr_fill(long n, float v, float *b, hipStream_t s)
-{
-    TR_LAUNCH(tr_fill_kernel, n, n, v, b);
+    hipLaunchKernelGGL(tr_frame_tables_kernel, dim3((unsigned)((nf * tables.n + 63) / 64)), dim3(64), 0, s, tab, nf,
+                       tables);
     return hipGetLastError();
 }
 hipError_t tr_adam(long n, float *w, const float *g, float *m, float *v, float lr, float b1, float b2, float c1,
                    float c2, float eps, hipStream_t s)
 {
     TR_LAUNCH(tr_adam_kernel, n, n, w, g, m, v, lr, b1, b2, c1, c2, eps);
-    return hipGetLastError();
-}
-
-hipError_t tr_repack(int Cin, int Cout, int CK, int nch, int Cout_pad, const float *blob, float *packed, float *bias,
-                     hipStream_t s)
-{
-    TR_LAUNCH(tr_repack_kernel, (long)nch * 9 * CK * Cout_pad + Cout, Cin, Cout, CK, nch, Cout_pad, blob, packed,
-              bias);
     return hipGetLastError();
 }
 

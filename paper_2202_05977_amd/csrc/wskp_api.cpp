@@ -348,16 +348,13 @@ extern "C" wskp_status_t wskp_repvgg_merge(int cin, int cout, const float *w1, c
     return WSKP_OK;
 }
 
-// Writes the split kernel's weights from the handle's weight blob.
-static hipError_t pack_split(const wskp_ctx *h, hipStream_t s)
+// The packing of the split kernel's weights from the handle's weight blob.
+static void add_split_jobs(const wskp_ctx *h, PackJobs &jobs)
 {
-    hipError_t e = hipSuccess;
-    for (size_t k = 0; k < h->split.size() && e == hipSuccess; ++k) {
+    for (size_t k = 0; k < h->split.size(); ++k) {
         const LayerPlan &lp = h->split[k];
-        e = conv_split_pack(lp.Cin, lp.L.Cout, false, h->dmaster + h->blob_off[k],
-                            static_cast<char *>(h->dsplit) + lp.w_off, s);
+        jobs.add_split(lp.Cin, lp.L.Cout, false, h->dmaster + h->blob_off[k], static_cast<char *>(h->dsplit) + lp.w_off);
     }
-    return e;
 }
 
 extern "C" wskp_status_t wskp_create(const wskp_config_t *cfg, const float *host_weights,
@@ -539,7 +536,9 @@ extern "C" wskp_status_t wskp_create(const wskp_config_t *cfg, const float *host
         }
         e = hipMalloc(&h->dsplit, bytes);
         for (auto &lp : h->split) lp.L.w = static_cast<char *>(h->dsplit) + lp.w_off;
-        if (e == hipSuccess) e = pack_split(h, nullptr);
+        PackJobs jobs;
+        add_split_jobs(h, jobs);
+        if (e == hipSuccess) e = launch_conv_pack(jobs, nullptr);
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
         if (e != hipSuccess) {
             if (h->dsplit) (void)hipFree(h->dsplit);
@@ -1116,7 +1115,7 @@ extern "C" wskp_status_t wskp_backward(wskp_handle_t h, void *stream, int N, int
     wskp_status_t st = set_device(h);
     if (st != WSKP_OK) return st;
     hipError_t e = launch_decode_backward(h->dc, N, H, W, head, c, mod, grad_out, grad_head, grad_c,
-                                          ws, static_cast<hipStream_t>(stream));
+                                          ws, 0, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "backward launch", WSKP_E_LAUNCH);
     return WSKP_OK;
 }
@@ -1126,11 +1125,10 @@ extern "C" wskp_status_t wskp_backward(wskp_handle_t h, void *stream, int N, int
 // pass for a group of nf frames of one size, each frame's tensors
 // contiguous after the previous frame's.
 struct TrainScratch {
-    float *X, *head, *c, *mod, *gy, *gh, *gc, *dh, *dec, *partial, *in, *gin, *part;
+    float *X, *head, *c, *mod, *gy, *dh, *dec, *partial, *in, *part;
     float *wpk[2 * kMaxLevels];   // packed weights of each input-gradient conv (blob order)
-    float *zb;                    // zero bias
     float *ge[kMaxLevels], *gu[kMaxLevels];
-    FrameDesc *tab;               // frame table of the group's input-gradient convs
+    FrameDesc *tab;               // frame tables of the group's input-gradient convs, one after the other
     size_t bytes;
 };
 
@@ -1167,34 +1165,29 @@ static size_t train_plan(const wskp_ctx *h, int Hm, int Wm, int nf, char *base, 
     mx_part = std::max(mx_part, tr_wgrad_part_floats(Hm, Wm, ch[0], 2 * M, nf));
     const int ldh = head_grad_stride(M);
     // the input-gradient convs' packed weights (C_out of the forward conv
-    // in, C_in out: encoders >= 1, decoders, the head) and the zero bias
-    // come first, at offsets that do not depend on the frame size: they are
+    // in, C_in out: encoders >= 1, decoders, the head) come first, at offsets that do not depend on the frame size: they are
     // written once per call and serve every frame
     auto wf = [](int ci, int co) { return conv_split_weight_bytes(ci, co) / sizeof(float); };
     TrainScratch t{};
     for (int l = 1; l < L; ++l) t.wpk[l] = take(wf(ch[l], ch[l - 1]));
     for (int l = 0; l + 1 < L; ++l) t.wpk[L + (L - 2 - l)] = take(wf(ch[l], ch[l + 1] + ch[l]));
     t.wpk[2 * L - 1] = take(wf(2 * M, ch[0]));
-    t.zb = take(256);
     t.X = take(F * 10 * P);
     t.head = take(F * 2 * M * P);
     t.c = take(F * 3 * P);
     t.mod = take(F * 3 * P);
     t.gy = take(F * 3 * P);
-    t.gh = take(F * 2 * M * P);
-    t.gc = take(F * 3 * P);
     t.dh = take(F * ldh * P);
     t.dec = take(decode_backward_scratch_bytes(h->dc, nf, Hm, Wm) / sizeof(float));
     t.partial = take((size_t)std::min(nf, kTrGroup) * tr_smape_blocks(3 * P));
     t.in = take(F * mx_in);
-    t.gin = take(F * mx_in);
     t.part = take(mx_part);
     for (int l = 0; l < L; ++l) {
         const size_t n = F * ch[l] * (Hm >> l) * (Wm >> l);
         t.ge[l] = take(n);
         t.gu[l] = l + 1 < L ? take(n) : nullptr;
     }
-    t.tab = reinterpret_cast<FrameDesc *>(take((F * sizeof(FrameDesc) + sizeof(float) - 1) / sizeof(float)));
+    t.tab = reinterpret_cast<FrameDesc *>(take(2 * kMaxLevels * F * sizeof(FrameDesc) / sizeof(float)));
     t.bytes = o;
     if (ts) *ts = t;
     return o;
@@ -1271,69 +1264,52 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
     long Ptot = 0;
     for (int i = 0; i < n; ++i) Ptot += (long)Hs[i] * Ws[i];
     const float inv_n = (float)(1.0 / (3.0 * (double)Ptot));
-    const size_t nw = wskp_num_weights(&h->cfg);
     const float *mw = h->dmaster;
     const size_t head_k = h->layers.size() - 1;
     auto wofs = [&](size_t k) { return mw + h->blob_off[k]; };
     auto gofs = [&](size_t k) { return grad + h->blob_off[k]; };
     auto bofs = [&](size_t k, int Ci, int Co) { return grad + h->blob_off[k] + (size_t)Ci * Co * 9; };
-    hipError_t e = tr_fill((long)nw, 0.f, grad, s);
-    // input gradient of conv k (Ci -> Co forward): gin = conv(gm, w flipped,
-    // in and out channels swapped), on the split kernel with the weights
-    // packed for it; gm has ldg >= Co channels (the head's 2M padded with
-    // zeros to a multiple of 16, the kernel's channel chunk; Ci, a network
-    // width, is one already)
-    // gradients of nf frames, frame f's at gm + f sg, into gin + f si
-    auto dgrad = [&](const TrainScratch &t, size_t k, int Hl, int Wl, int Ci, int ldg, int nf, const float *gm,
-                     long sg, float *gin, long si) -> hipError_t {
+    hipError_t e;
+    // Input gradient of conv k (Ci -> Co forward) of nf frames, on the split
+    // kernel with the weights packed for it: gm, with ldg >= Co channels (the
+    // head's 2M padded with zeros to a multiple of 16, the kernel's channel
+    // chunk; Ci, a network width, is one already), through the epilogue epi
+    // (Cu: the upsampled channels of a decoder's input) to the operands of
+    // `ops`; tab: their table of nf frames
+    auto dgrad = [&](const TrainScratch &t, size_t k, int epi, int Ci, int ldg, int Cu, int nf, const TrConvFrames &ops,
+                     const FrameDesc *tab) -> hipError_t {
         ConvLayer c{};
-        c.level = 0;
-        c.src0_kind = 0;
-        c.src0_idx = 0;
-        c.src1_idx = 0;
         c.C0 = ldg;
-        c.C1 = 0;
+        c.C1 = Cu;
         c.ks = 3;
         c.Cout = Ci;
         conv_split_layer(c, ldg);
         c.pool_idx = -1;
-        c.out_kind = 0;
-        c.out_idx = 1;
-        c.M = 0;
         c.in_qscale = 1.f;
         c.w = t.wpk[k];
-        c.bias = t.zb;
         FrameArg fa{};
         fa.n = nf;
-        if (nf == 1) {
-            fa.one.H = Hl;
-            fa.one.W = Wl;
-            fa.one.e[0] = const_cast<float *>(gm);
-            fa.one.e[1] = gin;
-        } else {
-            hipError_t te = tr_frame_table(t.tab, nf, Hl, Wl, gm, sg, gin, si, s);
-            if (te != hipSuccess) return te;
-            fa.table = t.tab;
-        }
-        const std::vector<int> hv(nf, Hl), wv(nf, Wl);
+        if (nf == 1) fa.one = tr_conv_frame(ops, 0);
+        else fa.table = tab;
+        const std::vector<int> hv(nf, ops.H), wv(nf, ops.W);
         int blocks = conv_grid(c, nf, hv.data(), wv.data());
-        if (blocks < 512) {   // as in plan_convs
+        if (blocks < 512 && epi != EPI_BWD_CAT) {   // as in plan_convs
             c.th = 4;
             blocks = conv_grid(c, nf, hv.data(), wv.data());
         }
-        return launch_conv_split(c, CONV_PLAIN, EPI_LINEAR, fa, blocks, s);
+        return launch_conv_split(c, CONV_PLAIN, epi, fa, blocks, s);
     };
     {
         TrainScratch t;
         train_plan(h, Hs[0], Ws[0], 1, static_cast<char *>(ws) + align_up(fwd), &t);
-        if (e == hipSuccess) e = tr_fill(256, 0.f, t.zb, s);
-        if (e == hipSuccess) e = conv_split_pack(2 * M, ch[0], true, wofs(head_k), t.wpk[head_k], s);
-        for (int l = 0; l + 1 < L && e == hipSuccess; ++l) {
+        PackJobs jobs;
+        jobs.add_split(2 * M, ch[0], true, wofs(head_k), t.wpk[head_k]);
+        for (int l = 0; l + 1 < L; ++l) {
             const size_t k = (size_t)L + (L - 2 - l);
-            e = conv_split_pack(ch[l], ch[l + 1] + ch[l], true, wofs(k), t.wpk[k], s);
+            jobs.add_split(ch[l], ch[l + 1] + ch[l], true, wofs(k), t.wpk[k]);
         }
-        for (int l = 1; l < L && e == hipSuccess; ++l)
-            e = conv_split_pack(ch[l], ch[l - 1], true, wofs(l), t.wpk[l], s);
+        for (int l = 1; l < L; ++l) jobs.add_split(ch[l], ch[l - 1], true, wofs(l), t.wpk[l]);
+        e = launch_conv_pack(jobs, s);
     }
     // Frames of one size run the backward pass as one group, every kernel
     // over all of them (frame k's tensors at a constant stride: fs floats
@@ -1379,9 +1355,9 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
             if (e == hipSuccess)
                 e = tr_smape(3 * P, kn, fr, eps_smape, inv_n, t.gy + k0 * 3 * P, t.partial, loss, f0 + k0 > 0, s);
         }
-        // decode adjoint over the group, then the weight activation's derivative
-        if (e == hipSuccess) e = launch_decode_backward(h->dc, nf, H, W, t.head, t.c, t.mod, t.gy, t.gh, t.gc, t.dec, s);
-        if (e == hipSuccess) e = tr_head_act_bwd(P, M, ldh, nf, t.gh, fd.head, fs, t.dh, s);
+        // decode adjoint over the group, through the weight activation
+        if (e == hipSuccess)
+            e = launch_decode_backward(h->dc, nf, H, W, t.head, t.c, t.mod, t.gy, t.dh, nullptr, t.dec, ldh, s);
         // Gradients of the activations, kept as gradients of their
         // pre-activations (the ReLU mask applied by the kernel that writes
         // the last contribution): gu[l] of u_l (l < L - 1; u_{L-1} is e_{L-1},
@@ -1390,39 +1366,48 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
         auto gu_of = [&](int l) { return l == L - 1 ? t.ge[l] : t.gu[l]; };
         auto act_of = [&](int l) { return l == L - 1 ? e_[L - 1] : u_[l]; };
         auto nel = [&](int l, int C) { return (long)C * (H >> l) * (W >> l); };   // one frame's floats
-        // head conv: input u_0, output 2M channels, no ReLU; u_0's gradient
-        // has one contribution, masked in place
+        // the input-gradient convs in launch order: the head (its gradient
+        // masked by u_0, its only contribution), the decoders, finest first
+        // (the concatenation's adjoint: u_{l+1}'s gradient, masked, its only
+        // contribution, and the first part of e_l's), the encoders, coarsest
+        // first (the 2x2 mean's adjoint: the last part of e_{l-1}'s, masked)
+        TrConvTables tb;
+        tb.t[tb.n++] = {H, W, t.dh, act_of(0), gu_of(0), nullptr, ldh * P, fs, nel(0, ch[0]), 0};
+        for (int l = 0; l + 1 < L; ++l)
+            tb.t[tb.n++] = {H >> l, W >> l, t.gu[l], act_of(l + 1), gu_of(l + 1), t.ge[l],
+                            nel(l, ch[l]), fs, nel(l + 1, ch[l + 1]), nel(l, ch[l])};
+        for (int l = L - 1; l >= 1; --l)
+            tb.t[tb.n++] = {H >> l, W >> l, t.ge[l], e_[l - 1], t.ge[l - 1], nullptr,
+                            nel(l, ch[l]), fs, nel(l - 1, ch[l - 1]), 0};
+        if (nf > 1 && e == hipSuccess) e = tr_frame_tables(t.tab, nf, tb, s);
+        int ti = 0;
+        auto input_grad = [&](size_t k, int epi, int Ci, int ldg, int Cu) {
+            const int i = ti++;
+            return dgrad(t, k, epi, Ci, ldg, Cu, nf, tb.t[i], t.tab + (size_t)i * nf);
+        };
+        const bool more = f0 > 0;   // gradients of the frames before are there
+        // head conv: input u_0, output 2M channels, no ReLU
         if (e == hipSuccess)
             e = tr_wgrad(H, W, 2 * M, ldh, nf, t.dh, ldh * P, u_[0], fs, ch[0], nullptr, 0, 0, t.part, gofs(head_k),
-                         bofs(head_k, ch[0], 2 * M), s);
-        if (e == hipSuccess) e = dgrad(t, head_k, H, W, ch[0], ldh, nf, t.dh, ldh * P, gu_of(0), nel(0, ch[0]));
-        if (e == hipSuccess) e = tr_mask(nel(0, ch[0]), nf, gu_of(0), act_of(0), fs, gu_of(0), s);
-        // decoders, finest first: dec_l is conv L + (L - 2 - l) in blob order;
-        // the concatenation's adjoint writes u_{l+1}'s gradient (masked, its
-        // only contribution) and the first part of e_l's
+                         bofs(head_k, ch[0], 2 * M), more, s);
+        if (e == hipSuccess) e = input_grad(head_k, EPI_BWD_MASK, ch[0], ldh, 0);
+        // decoders: dec_l is conv L + (L - 2 - l) in blob order
         for (int l = 0; l + 1 < L && e == hipSuccess; ++l) {
             const size_t k = (size_t)L + (L - 2 - l);
             const int Hl = H >> l, Wl = W >> l, Ci = ch[l + 1] + ch[l], Co = ch[l];
-            const float *gm = t.gu[l];
             // the input [upsampled u_{l+1}, e_l] is read from its two sources
-            e = tr_wgrad(Hl, Wl, Co, Co, nf, gm, nel(l, Co), e_[l], fs, ch[l], u_[l + 1], fs, ch[l + 1], t.part,
-                         gofs(k), bofs(k, Ci, Co), s);
-            if (e == hipSuccess) e = dgrad(t, k, Hl, Wl, Ci, Co, nf, gm, nel(l, Co), t.gin, nel(l, Ci));
-            if (e == hipSuccess)
-                e = tr_cat_bwd(Hl, Wl, ch[l + 1], ch[l], nf, t.gin, act_of(l + 1), fs, gu_of(l + 1), t.ge[l], s);
+            e = tr_wgrad(Hl, Wl, Co, Co, nf, t.gu[l], nel(l, Co), e_[l], fs, ch[l], u_[l + 1], fs, ch[l + 1], t.part,
+                         gofs(k), bofs(k, Ci, Co), more, s);
+            if (e == hipSuccess) e = input_grad(k, EPI_BWD_CAT, Ci, Co, ch[l + 1]);
         }
-        // encoders, coarsest first: enc_l is conv l; the 2x2 mean's adjoint
-        // adds the last part of e_{l-1}'s gradient and masks it
+        // encoders: enc_l is conv l
         for (int l = L - 1; l >= 1 && e == hipSuccess; --l) {
             const int Hl = H >> l, Wl = W >> l, Ci = ch[l - 1], Co = ch[l];
-            const float *gm = t.ge[l];
             e = tr_pool(H >> (l - 1), W >> (l - 1), Ci, nf, e_[l - 1], fs, t.in, s);
             if (e == hipSuccess)
-                e = tr_wgrad(Hl, Wl, Co, Co, nf, gm, nel(l, Co), t.in, nel(l, Ci), Ci, nullptr, 0, 0, t.part, gofs(l),
-                             bofs(l, Ci, Co), s);
-            if (e == hipSuccess) e = dgrad(t, (size_t)l, Hl, Wl, Ci, Co, nf, gm, nel(l, Co), t.gin, nel(l, Ci));
-            if (e == hipSuccess)
-                e = tr_pool_bwd(H >> (l - 1), W >> (l - 1), Ci, nf, t.gin, e_[l - 1], fs, t.ge[l - 1], s);
+                e = tr_wgrad(Hl, Wl, Co, Co, nf, t.ge[l], nel(l, Co), t.in, nel(l, Ci), Ci, nullptr, 0, 0, t.part,
+                             gofs(l), bofs(l, Ci, Co), more, s);
+            if (e == hipSuccess) e = input_grad((size_t)l, EPI_BWD_POOL, Ci, Co, 0);
         }
         // first encoder: the network input written out, weight gradient only
         for (int k0 = 0; k0 < nf && e == hipSuccess; k0 += kTrGroup) {
@@ -1432,7 +1417,7 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
         }
         if (e == hipSuccess)
             e = tr_wgrad(H, W, ch[0], ch[0], nf, t.ge[0], nel(0, ch[0]), t.X, 10 * P, 10, nullptr, 0, 0, t.part,
-                         gofs(0), bofs(0, 10, ch[0]), s);
+                         gofs(0), bofs(0, 10, ch[0]), more, s);
         fbase += nf * fbytes;
     }
     if (e != hipSuccess) return hip_fail(e, "training launch", WSKP_E_LAUNCH);
@@ -1452,16 +1437,15 @@ extern "C" wskp_status_t wskp_adam(wskp_handle_t h, void *stream, const float *g
     const float c1 = (float)(1.0 - std::pow((double)beta1, step)), c2 = (float)(1.0 - std::pow((double)beta2, step));
     hipError_t e = tr_adam((long)nw, h->dmaster, grad, m, v, lr, beta1, beta2, c1, c2, eps, s);
     // the conv kernels read the weights in their own layouts: repack each conv
-    std::vector<std::pair<int, int>> d;
-    conv_dims(&h->cfg, d);
-    for (size_t k = 0; k < h->layers.size() && e == hipSuccess; ++k) {
+    PackJobs jobs;
+    for (size_t k = 0; k < h->layers.size(); ++k) {
         const LayerPlan &lp = h->layers[k];
-        const int nch = lp.L.Cin_pad / lp.L.CK;
-        e = tr_repack(d[k].first, d[k].second, lp.L.CK, nch, lp.L.Cout_pad, h->dmaster + h->blob_off[k],
-                      reinterpret_cast<float *>(static_cast<char *>(h->dweights) + lp.w_off),
-                      reinterpret_cast<float *>(static_cast<char *>(h->dweights) + lp.b_off), s);
+        char *dw = static_cast<char *>(h->dweights);
+        jobs.add_native(lp.Cin, lp.L.Cout, lp.L.CK, lp.L.Cin_pad / lp.L.CK, lp.L.Cout_pad, h->dmaster + h->blob_off[k],
+                        reinterpret_cast<float *>(dw + lp.w_off), reinterpret_cast<float *>(dw + lp.b_off));
     }
-    if (e == hipSuccess) e = pack_split(h, s);
+    add_split_jobs(h, jobs);
+    if (e == hipSuccess) e = launch_conv_pack(jobs, s);
     if (e != hipSuccess) return hip_fail(e, "adam launch", WSKP_E_LAUNCH);
     return WSKP_OK;
 }

@@ -206,9 +206,8 @@ __device__ __forceinline__ int batch_tile_id(const FrameArg &fa, int b, int nb, 
 
 
 enum ConvMode { CONV_PACK = 0, CONV_POOL = 1, CONV_CAT = 2, CONV_PLAIN = 3 };
-// EPI_LINEAR: bias only, NHWC fp32 store (the input gradient of a conv in
-// training runs the split kernel with transposed, flipped weights).
-enum ConvEpi { EPI_RELU = 0, EPI_HEAD_SOFTPLUS = 1, EPI_HEAD_EXP = 2, EPI_LINEAR = 3 };
+// EPI_BWD_*: the input gradient of a conv in training (conv_split.hip).
+enum ConvEpi { EPI_RELU = 0, EPI_HEAD_SOFTPLUS = 1, EPI_HEAD_EXP = 2, EPI_BWD_MASK = 3, EPI_BWD_CAT = 4, EPI_BWD_POOL = 5 };
 enum ActType { ACT_F32 = 0, ACT_BF16 = 1 };
 
 // One 3x3 conv layer as the kernels see it.
@@ -255,12 +254,26 @@ hipError_t launch_conv(const ConvLayer &L, int mode, int epi, int prec, const Fr
                        int blocks, hipStream_t s);
 int conv_grid(const ConvLayer &L, int n, const int *H, const int *W);
 // FP32 3x3 convs on the bf16 matrix cores (conv_split.hip): sets the layer's
-// tiling for Cin input channels (Cout set), sizes and writes its packed
-// weights (from w [Cout][Cin][3][3] on the device; dgrad: w is [Cin][Cout][3][3]
-// and the conv is its input gradient), launches it.
+// tiling for Cin input channels (Cout set), sizes its packed weights, launches
+// it.
 void conv_split_layer(ConvLayer &L, int Cin);
 size_t conv_split_weight_bytes(int Cin, int Cout);
-hipError_t conv_split_pack(int Cin, int Cout, bool dgrad, const float *w, void *packed, hipStream_t s);
+// fp32 weights packed on the device, every layer in one launch
+enum PackKind { PACK_SPLIT = 0, PACK_SPLIT_DGRAD = 1, PACK_NATIVE = 2 };
+struct PackJob {
+    int kind, Ci, Co, nch, groups, CK, Cout_pad, block0;
+    const float *w;
+    void *out;
+    float *bias;
+};
+constexpr int kMaxPackJobs = 4 * kMaxLevels;   // both layouts of 2 levels - 1 convs and the head
+struct PackJobs {
+    int n = 0, blocks = 0;
+    PackJob j[kMaxPackJobs];
+    void add_split(int Ci, int Co, bool dgrad, const float *w, void *out);
+    void add_native(int Ci, int Co, int CK, int nch, int Cout_pad, const float *w, float *out, float *bias);
+};
+hipError_t launch_conv_pack(const PackJobs &jobs, hipStream_t s);
 hipError_t launch_conv_split(const ConvLayer &L, int mode, int epi, const FrameArg &fa, int blocks, hipStream_t s);
 int conv_chunk(int prec, int mode, int Cin, int C0);
 // 16-channel output blocks per workgroup for a layer with nblk blocks.
@@ -280,9 +293,12 @@ hipError_t launch_decode_tensors(const DecodeCfg &dc, int N, int H, int W, const
 // the l times pooled c, no remodulation
 hipError_t launch_decode_levels(const DecodeCfg &dc, int levels, int H, int W, const float *const *heads,
                                 const float *c, float *const *outs, hipStream_t s);
+// act_ld > 0 (training): grad_head receives the gradient of the head conv's
+// output instead, rows of act_ld >= 2M floats: the weights' part times
+// softplus' (= -expm1(-W)), the logits', zeros; grad_c is not written.
 hipError_t launch_decode_backward(const DecodeCfg &dc, int N, int H, int W, const float *head,
                                   const float *c, const float *mod, const float *g,
-                                  float *grad_head, float *grad_c, void *scratch,
+                                  float *grad_head, float *grad_c, void *scratch, int act_ld,
                                   hipStream_t s);
 size_t decode_backward_scratch_bytes(const DecodeCfg &dc, int N, int H, int W);
 // Training kernels (train.hip): see the file's header for each operation.
@@ -306,11 +322,6 @@ int tr_smape_blocks(long n);
 // tr_smape_blocks(n) floats)
 hipError_t tr_smape(long n, int nf, const TrFrames &fr, float eps, float inv_n, float *g, float *partial, float *loss,
                     int accumulate, hipStream_t s);
-// dh[p][j] for j < 2M, zero for 2M <= j < ld (rows ld floats apart)
-hipError_t tr_head_act_bwd(long P, int M, int ld, int nf, const float *grad_head, const float *planar, long sp,
-                           float *dh, hipStream_t s);
-// gm = (act > 0) g over nf frames of n values (gm may be g)
-hipError_t tr_mask(long n, int nf, const float *g, const float *act, long sa, float *gm, hipStream_t s);
 // partial sums of a weight gradient over nf frames
 size_t tr_wgrad_part_floats(int H, int W, int Ci, int Co, int nf);
 // its kernel (train_wgrad.hip) and the number of partial sums it writes
@@ -320,24 +331,38 @@ hipError_t launch_wgrad_split(int H, int W, int Co, int ldg, int nf, const float
                               hipStream_t s);
 // The conv's input: Cu channels of `up` (H/2 x W/2) upsampled x2, then Cf
 // channels of `in` (H x W) (Cu = 0: `in` alone); gm rows are ldg >= Co
-// floats apart; dw and db accumulate the nf frames
+// floats apart; dw and db receive the sum of the nf frames, added to what is
+// there if accumulate
 hipError_t tr_wgrad(int H, int W, int Co, int ldg, int nf, const float *gm, long sgm, const float *in, long sin,
-                    int Cf, const float *up, long sup, int Cu, float *part, float *dw, float *db, hipStream_t s);
-// gu = (act_u > 0) * (the upsampled part's gradient); ge = the skip part's
-hipError_t tr_cat_bwd(int H, int W, int Cu, int Ce, int nf, const float *gcat, const float *act_u, long sa, float *gu,
-                      float *ge, hipStream_t s);
-// ge = (act > 0) * (ge + the 2x2 mean's adjoint of gp)
-hipError_t tr_pool_bwd(int H, int W, int C, int nf, const float *gp, const float *act, long sa, float *ge,
-                       hipStream_t s);
-// table of nf frames of H x W for an input-gradient conv: e[0] = src + f ss,
-// e[1] = dst + f sd
-hipError_t tr_frame_table(FrameDesc *tab, int nf, int H, int W, const float *src, long ss, float *dst, long sd,
-                          hipStream_t s);
-hipError_t tr_fill(long n, float v, float *b, hipStream_t s);
+                    int Cf, const float *up, long sup, int Cu, float *part, float *dw, float *db, bool accumulate,
+                    hipStream_t s);
+// Tables of nf frames for the input-gradient convs, all in one launch: table k's
+// descriptors at tab + k nf, of H x W with e[0] = src, e[1] = dst, e[2] = dst2,
+// u[0] = act of the frame (frame strides in floats).
+struct TrConvFrames {
+    int H, W;
+    const float *src, *act;
+    float *dst, *dst2;
+    long ss, sa, sd, sd2;
+};
+struct TrConvTables {
+    int n = 0;
+    TrConvFrames t[2 * kMaxLevels];
+};
+__host__ __device__ inline FrameDesc tr_conv_frame(const TrConvFrames &t, int f)
+{
+    FrameDesc d{};
+    d.H = t.H;
+    d.W = t.W;
+    d.e[0] = const_cast<float *>(t.src + f * t.ss);
+    d.e[1] = t.dst + f * t.sd;
+    d.e[2] = t.dst2 ? t.dst2 + f * t.sd2 : nullptr;
+    d.u[0] = t.act ? const_cast<float *>(t.act + f * t.sa) : nullptr;
+    return d;
+}
+hipError_t tr_frame_tables(FrameDesc *tab, int nf, const TrConvTables &tables, hipStream_t s);
 hipError_t tr_adam(long n, float *w, const float *g, float *m, float *v, float lr, float b1, float b2, float c1,
                    float c2, float eps, hipStream_t s);
-hipError_t tr_repack(int Cin, int Cout, int CK, int nch, int Cout_pad, const float *blob, float *packed, float *bias,
-                     hipStream_t s);
 // Multi-resolution reconstruction pieces (mr.hip): 2x2 mean of a 3-channel
 // image, and the Eq. 7 blend (optionally remodulated).
 hipError_t launch_pool2(int H, int W, const float *in, float *out, hipStream_t s);

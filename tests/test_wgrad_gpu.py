@@ -16,10 +16,14 @@ pytestmark = pytest.mark.gpu
 # of both signs after an fp32 forward pass
 TOL_GRAD = 1e-4
 ODD = synth.NetConfig(levels=2, channels=(48, 80), kernel_sizes=(3, 5))      # blocks of 32 across the sources at 80
+# input gradients through a pool and a concatenation on the same activation, the
+# blocks of 32 of the concatenations cut across their sources, M = 1
+NEST = synth.NetConfig(levels=4, channels=(16, 48, 32, 16), kernel_sizes=(3,))
 NARROW = synth.NetConfig(levels=1, channels=(16,), kernel_sizes=(3,))        # 16 channels, 2 outputs
 
 
 @pytest.mark.parametrize("cfg,sizes", [(ODD, [(2, 2)]), (ODD, [(34, 66)] * 2), (ODD, [(10, 130), (66, 6)]),
+                                       (NEST, [(24, 40), (16, 8), (24, 40)]),
                                        (NARROW, [(33, 31)]), (NARROW, [(70, 97)] * 2)])
 def test_weight_gradients_against_oracle(cfg, sizes):
     from paper_2202_05977_amd import wskp

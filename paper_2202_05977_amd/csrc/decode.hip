@@ -602,12 +602,14 @@ __global__ __launch_bounds__(kFThreads, 4) void decode_tile_kernel(DecodeCfg dc,
         }
     }
     // the thread's centres: column cx of the tile, rows cy .. cy + kNC - 1
-    // (the last run of a column is moved up to end at row TH - 1; centres it
-    // shares with the run above are computed, and stored, twice with the
-    // same values).  nc: how many of them lie in the image.
+    // (the last run of a column is moved up to end at row TH - 1; the centres it
+    // shares with the run above are that run's to store: the two sum a window
+    // in different orders).  nc: how many of them lie in the image; q0: the
+    // first that this thread stores.
     const int nv_items = TW * ((TH + kNC - 1) / kNC);
     const bool owner = tid < nv_items;
     const int cx = tid % TW, cy = min((tid / TW) * kNC, TH - kNC);
+    const int q0 = (tid / TW) * kNC - cy;
     const int gcx = x0 + cx, gcy = y0 + cy;
     const int nc = (owner && gcx < W) ? max(0, min(kNC, H - gcy)) : 0;
     auto centre_off = [&](int q) { return q < nc ? (unsigned)((gcy + q) * W + gcx) * 4u : kNoPixel; };
@@ -801,6 +803,7 @@ __global__ __launch_bounds__(kFThreads, 4) void decode_tile_kernel(DecodeCfg dc,
 #pragma unroll
     for (int q = 0; q < kNC; ++q) {
         if (q >= nc) break;
+        if (q < q0) continue;
         const float inv = 1.f / esum[q];
         float *op = io.out + centre_pix(q) * 3;
 #pragma unroll

@@ -401,7 +401,7 @@ __device__ __forceinline__ void conv_epilogue(const ConvLayer &L, const FrameDes
 {
     constexpr int MB = TH / 2;
     constexpr int NC = NB * 16;
-    constexpr bool CAN_POOL = !std::is_same<OutT, float>::value && EPI == EPI_RELU && MB >= 4;
+    constexpr bool CAN_POOL = !std::is_same<OutT, float>::value && EPI == EPI_RELU && MB >= 4 && PREC == 1;
     // bf16 activations of an even number of blocks: stored in pairs
     constexpr bool PAIR = !std::is_same<OutT, float>::value && EPI == EPI_RELU && NB % 2 == 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -775,6 +775,7 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
 #define WSKP_CONV_DIRECT 1
 #endif
 constexpr int kTH = WSKP_CONV_TH;
+constexpr int kTH8 = 4;
 // the network-input layer (one reduction chunk) gets its own knob
 #ifndef WSKP_PACK_TH
 #define WSKP_PACK_TH 8
@@ -803,7 +804,7 @@ bool conv_uses_direct(int prec, int mode, int CK, int ks) { return uses_direct(p
 int conv_tile_rows(int prec, int mode, int CK, int level, bool pool, int ks)
 {
     if (mode == CONV_PACK) return kTHP;
-    if (!uses_direct(prec, mode, CK, ks)) return kTH;
+    if (!uses_direct(prec, mode, CK, ks)) return prec == 2 ? kTH8 : kTH;
     return (level >= WSKP_COARSE_LEVEL && !pool) ? 4 : kTHD;
 }
 
@@ -843,11 +844,60 @@ int conv_grid(const ConvLayer &L, int n, const int *H, const int *W)
     return (int)total;
 }
 
+// FP32 layers of few pixels: a workgroup's time is its serial chain of MFMAs
+// (32 cycles each, TH/2 NB of them per four input channels and tap), so
+// below two workgroups per CU first the output blocks of a workgroup, then its
+// rows are cut: at (2 rows, 1 block) the chain is an eighth of that at (4, 4).
+// A wider grid costs re-reads of the input tile and of the halo, which pay only
+// while CUs are idle.  The weights' layout and every output's order of
+// summation do not depend on the tiling.  The small net, us at 16x16 / 128x128 /
+// 256x256 / 320x400: 69 / 74 / 81 / 125 without the rule, 41 / 43 / 61 / 109 at
+// this line, 41 / 43 / 62 / 120 at 256 workgroups, 41 / 43 / 61 / 110 at 1024; the
+// 5-level net at 64x64 / 256x256: 235 / 270 -> 90 / 176.  A training step of
+// 8 crops of 256x256 is 1 % slower at 1024 than here, 3 % at 2048.
+constexpr int kFp32Grid = 512;
+
+int conv_fp32_tiles(ConvLayer &L, int n, const int *H, const int *W)
+{
+    int blocks = conv_grid(L, n, H, W);
+    const int nblk = L.Cout_pad / 16;
+    while (blocks < kFp32Grid && L.NB > 1) {
+        do --L.NB;
+        while (nblk % L.NB);
+        L.groups = nblk / L.NB;
+        blocks = conv_grid(L, n, H, W);
+    }
+    while (blocks < kFp32Grid && L.th > 2) {
+        L.th /= 2;
+        blocks = conv_grid(L, n, H, W);
+    }
+    return blocks;
+}
+
+// The cut tiles of conv_fp32_tiles: TH rows, one block.
+template <int MODE, int EPI, int TH, int CK>
+static bool launch_fp32_small(const ConvLayer &L, const FrameArg &fa, int blocks, hipStream_t s)
+{
+    if (L.th != TH) return false;
+    if (L.ks == 5)
+        hipLaunchKernelGGL((conv3x3_kernel<0, MODE, EPI, TH, CK, 1, float, float, 5>), dim3(blocks), dim3(kThreads), 0,
+                           s, L, fa);
+    else
+        hipLaunchKernelGGL((conv3x3_kernel<0, MODE, EPI, TH, CK, 1, float, float>), dim3(blocks), dim3(kThreads), 0, s,
+                           L, fa);
+    return true;
+}
+
 template <int PREC, int MODE, int EPI, int CK, int NB, typename OutT>
 static void launch_one(const ConvLayer &L, const FrameArg &fa, int blocks, hipStream_t s)
 {
     using SrcT = typename std::conditional<PREC == 0, float, unsigned short>::type;
-    constexpr int TH = MODE == CONV_PACK ? kTHP : kTH;
+    constexpr int TH = MODE == CONV_PACK ? kTHP : PREC == 2 ? kTH8 : kTH;
+    if constexpr (PREC == 0 && NB == 1) {
+        if (launch_fp32_small<MODE, EPI, 2, CK>(L, fa, blocks, s)) return;
+        if constexpr (TH == 8)
+            if (launch_fp32_small<MODE, EPI, 4, CK>(L, fa, blocks, s)) return;
+    }
     if constexpr (WSKP_CONV_DIRECT && NB == 1 && PREC == 1 && CK == 32 && (MODE == CONV_CAT || MODE == CONV_PLAIN)) {
         if (L.ks == 5) {
             if (L.th == 4)

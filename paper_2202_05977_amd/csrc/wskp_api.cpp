@@ -124,7 +124,9 @@ struct wskp_ctx {
         hipStream_t s;
         bool reverse;
         std::vector<int> caps;   // workgroups of each launch
-        std::vector<int> rows;   // tile rows of each conv launch, negative on the split kernel
+        // each conv launch's tile rows and blocks per group, rows negative on
+        // the split kernel; the decode's tile rows
+        std::vector<int> rows;
         hipGraphExec_t exec;
         char *tab;               // device: header + descriptors
     };
@@ -748,6 +750,7 @@ static std::vector<ConvGroup> plan_convs(const wskp_ctx *h, int n, const int *Hs
             ConvLaunch c{lp.L, lp.mode, lp.epi, split, 0};
             if (runs_conv_bf16(h->prec, lp)) c.L.th = conv_bf16_rows(c.L, g.n, Hs + f, Ws + f);
             c.blocks = conv_grid(c.L, g.n, Hs + f, Ws + f);
+            if (h->prec == WSKP_PREC_FP32 && !split) c.blocks = conv_fp32_tiles(c.L, g.n, Hs + f, Ws + f);
             // 4-row tiles where 8-row ones leave CUs without their two workgroups
             if (split && c.blocks < 512) {
                 c.L.th = 4;
@@ -788,7 +791,8 @@ static wskp_status_t run_frames(wskp_ctx *h, const FrameArg &fa, int n, const in
         }
         if (ev) (void)hipEventRecord(ev[++k], s);
     }
-    hipError_t e = launch_decode_frames(h->dc, fa, decode_grid(h->dc, n, Hs, Ws), s);
+    const DecodeCfg dc = decode_frames_cfg(h->dc, n, Hs, Ws);
+    hipError_t e = launch_decode_frames(dc, fa, decode_grid(dc, n, Hs, Ws), s);
     if (e != hipSuccess) return hip_fail(e, "decode launch", WSKP_E_LAUNCH);
     if (ev) (void)hipEventRecord(ev[++k], s);
     return WSKP_OK;
@@ -916,7 +920,8 @@ static int next_pow2(int v)
 // executable graph whose launches read the frame count and the descriptors
 // from the device buffer c.tab (header, then descriptors), on the handle's
 // own capture stream.
-static wskp_status_t capture_batch_graph(wskp_ctx *h, wskp_ctx::BatchGraph &c, const std::vector<ConvGroup> &groups)
+static wskp_status_t capture_batch_graph(wskp_ctx *h, wskp_ctx::BatchGraph &c, const std::vector<ConvGroup> &groups,
+                                         const DecodeCfg &dc)
 {
     hipError_t e;
     if (!h->cap_stream && (e = hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking)) != hipSuccess)
@@ -944,7 +949,7 @@ static wskp_status_t capture_batch_graph(wskp_ctx *h, wskp_ctx::BatchGraph &c, c
     }
     fa.dev_n = hdr + 2 * kHeaderInts;
     fa.launch = 0;
-    if (le == hipSuccess) le = launch_decode_frames(h->dc, fa, c.caps.back(), cs);
+    if (le == hipSuccess) le = launch_decode_frames(dc, fa, c.caps.back(), cs);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(cs, &graph);
     if (le != hipSuccess || e != hipSuccess) {
@@ -1009,6 +1014,7 @@ extern "C" wskp_status_t wskp_denoise_batch(wskp_handle_t h, void *stream, int n
         Ht[i] = Hs[order[i]];
         Wt[i] = Ws[order[i]];
     }
+    const DecodeCfg dc = decode_frames_cfg(h->dc, n, Ht.data(), Wt.data());
     std::vector<ConvGroup> groups;
     if (flags & WSKP_BATCH_GRAPH) {
         groups = plan_convs(h, n, Ht.data(), Wt.data());
@@ -1017,13 +1023,15 @@ extern "C" wskp_status_t wskp_denoise_batch(wskp_handle_t h, void *stream, int n
             for (const ConvLaunch &c : cg.convs) {
                 caps.push_back(next_pow2(c.blocks));
                 rows.push_back(c.split ? -c.L.th : c.L.th);
+                rows.push_back(c.L.NB);
             }
-        caps.push_back(next_pow2(decode_grid(h->dc, n, Ht.data(), Wt.data())));
+        caps.push_back(next_pow2(decode_grid(dc, n, Ht.data(), Wt.data())));
+        rows.push_back(dc.th);
         for (auto &c : h->graphs)
             if (c.s == s && c.reverse == reverse && c.caps == caps && c.rows == rows) g = &c;
         if (!g && h->graphs.size() < kMaxGraphs) {
             wskp_ctx::BatchGraph c{s, reverse, caps, rows, nullptr, nullptr};
-            if ((st = capture_batch_graph(h, c, groups)) != WSKP_OK) return st;
+            if ((st = capture_batch_graph(h, c, groups, dc)) != WSKP_OK) return st;
             h->graphs.push_back(c);
             g = &h->graphs.back();
         }
@@ -1044,7 +1052,7 @@ extern "C" wskp_status_t wskp_denoise_batch(wskp_handle_t h, void *stream, int n
     }
     hdr[2 * kHeaderInts] = 0;
     hdr[2 * kHeaderInts + 1] = n;
-    hdr[2 * kHeaderInts + 2] = decode_grid(h->dc, n, Ht.data(), Wt.data());
+    hdr[2 * kHeaderInts + 2] = decode_grid(dc, n, Ht.data(), Wt.data());
     // (workspace regions in the caller's order)
     std::vector<char *> base(n);
     char *at = static_cast<char *>(ws) + table_bytes(n);

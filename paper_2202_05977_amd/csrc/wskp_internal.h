@@ -226,7 +226,7 @@ struct ConvLayer {
     int M;             // head: channels 0..M-1 get the weight activation
     int CK;            // input channels per reduction chunk (weights packed to match)
     int NB;            // 16-channel output blocks per workgroup
-    int th;            // output rows per tile of the kernel that runs this layer
+    int th;            // output rows per tile of the kernel that runs this layer (TH of its template)
     int ks;            // kernel size: 3, or 5 (a merged RepVGG block)
     int pool_idx;      // >= 0: the epilogue also writes the 2x2 means of the output to p[pool_idx]
     const void *w;     // packed weights
@@ -253,6 +253,8 @@ struct DecodeCfg {
 hipError_t launch_conv(const ConvLayer &L, int mode, int epi, int prec, const FrameArg &fa,
                        int blocks, hipStream_t s);
 int conv_grid(const ConvLayer &L, int n, const int *H, const int *W);
+// fp32 native convs: sets the layer's tiling for these sizes, returns its grid
+int conv_fp32_tiles(ConvLayer &L, int n, const int *H, const int *W);
 // FP32 3x3 convs on the bf16 matrix cores (conv_split.hip): sets the layer's
 // tiling for Cin input channels (Cout set), sizes its packed weights, launches
 // it.
@@ -287,6 +289,8 @@ hipError_t launch_decode_frames(const DecodeCfg &dc, const FrameArg &fa, int blo
 // Sets dc.tw, dc.th, dc.hxs from dc.R (the forward decode's tile shape).
 void decode_tile_shape(DecodeCfg &dc);
 int decode_grid(const DecodeCfg &dc, int n, const int *H, const int *W);
+// the forward decode's tile for a batch of these sizes
+DecodeCfg decode_frames_cfg(const DecodeCfg &dc, int n, const int *H, const int *W);
 hipError_t launch_decode_tensors(const DecodeCfg &dc, int N, int H, int W, const float *head,
                                  const float *c, const float *mod, float *out, hipStream_t s);
 // wskp_decode of 1..3 levels of one frame in one launch, level l's irradiance

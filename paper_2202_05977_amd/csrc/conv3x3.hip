@@ -508,10 +508,7 @@ __device__ __forceinline__ void conv_epilogue(const ConvLayer &L, const FrameDes
 }
 
 template <int PREC, int MODE, int EPI, int TH, int CK, int NB, typename SrcT, typename OutT, int KS = 3>
-#ifndef WSKP_CONV_MIN_WG
-#define WSKP_CONV_MIN_WG 1
-#endif
-__global__ __launch_bounds__(kThreads, (MODE == CONV_PACK && PREC == 1 && KS == 3) ? 4 : WSKP_CONV_MIN_WG) void conv3x3_kernel(ConvLayer L, FrameArg fa)
+__global__ __launch_bounds__(kThreads, (MODE == CONV_PACK && PREC == 1 && KS == 3) ? 4 : 1) void conv3x3_kernel(ConvLayer L, FrameArg fa)
 {
     using S = Stage<PREC, MODE, CK, TH, NB, SrcT, KS>;
     constexpr int MB = TH / 2;
@@ -775,7 +772,12 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
 #define WSKP_CONV_DIRECT 1
 #endif
 constexpr int kTH = WSKP_CONV_TH;
-constexpr int kTH8 = 4;
+// fp8: 8 rows, so that a weight fragment read from LDS serves four blocks of 16
+// pixels instead of two and the halo is a third instead of half of the tile; its time
+// goes to LDS reads and the quantisation while staging.  1080p, five levels:
+// 632 us with 4 rows, 557 with 8 (the full-resolution decoder 150 -> 127, the head
+// 94 -> 76, the widest decoder 105 -> 82).
+constexpr int kTH8 = 8;
 // the network-input layer (one reduction chunk) gets its own knob
 #ifndef WSKP_PACK_TH
 #define WSKP_PACK_TH 8

@@ -156,10 +156,10 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ unsigned fp8x4(float a, float b, float c, float d)
 {
     const float m = 448.f;
-    a = fminf(fmaxf(a, -m), m);
-    b = fminf(fmaxf(b, -m), m);
-    c = fminf(fmaxf(c, -m), m);
-    d = fminf(fmaxf(d, -m), m);
+    a = __builtin_amdgcn_fmed3f(a, -m, m);
+    b = __builtin_amdgcn_fmed3f(b, -m, m);
+    c = __builtin_amdgcn_fmed3f(c, -m, m);
+    d = __builtin_amdgcn_fmed3f(d, -m, m);
     int r = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
     r = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, r, true);
     return (unsigned)r;

@@ -142,18 +142,22 @@ def _check(status: int, where: str):
 def _ptr(t: Optional[torch.Tensor], name: str, shape: Optional[Sequence[int]] = None):
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if t.dtype != torch.float32 or not t.is_contiguous():
         raise TypeError(f"{name} must be contiguous float32")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     return ctypes.c_void_p(t.data_ptr())
 
 
 def _stream(stream) -> ctypes.c_void_p:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream's handle without a Stream object: building one takes
+        # 3 us, and 15 us on autograd's thread
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 

@@ -34,6 +34,9 @@
 
 namespace wskp {
 
+template <int EPI>
+constexpr bool kHead = EPI == EPI_HEAD_SOFTPLUS || EPI == EPI_HEAD_EXP;
+
 // =============================================================================
 // Staging of one reduction chunk: the (TH+KS-1) x (32+KS-1) input halo
 // (virtual channels [cc*CK, cc*CK+CK)) and the weight slice.  init() computes each
@@ -263,18 +266,28 @@ struct Stage {
     }
 };
 
+// The head's weight rows enter the MFMA in the order 0, 4, 8, 12, 1, 5, ...: row
+// 4 q + k of the product is channel 4 k + q, so that register k of every lane
+// holds channels 4 k .. 4 k + 3 and the epilogue evaluates the weight activation
+// for ceil(M / 4) registers instead of all four, and skips those past 2M.
+template <bool HEAD>
+__device__ __forceinline__ int weight_row(int lj)
+{
+    return HEAD ? ((lj & 3) << 2) | (lj >> 2) : lj;
+}
+
 // One chunk's MFMAs.  fp32: KS*KS*CK/4 steps of v_mfma_f32_16x16x4f32 (K
 // order tap, channel); bf16: NK steps of v_mfma_f32_16x16x32_bf16, each
 // covering 32 consecutive K values as 4 runs of 8 channels (a run never
 // crosses a tap because CK is a multiple of 8; for CK = 16 one MFMA spans
 // two taps).
-template <int PREC, int MODE, int CK, int TH, int NB, typename SrcT, int KS>
+template <int PREC, int MODE, bool HEAD, int CK, int TH, int NB, typename SrcT, int KS>
 __device__ __forceinline__ void chunk_mfma(const void *As_, const void *Bs_, f32x4 (*acc)[NB])
 {
     using S = Stage<PREC, MODE, CK, TH, NB, SrcT, KS>;
     constexpr int MB = TH / 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int lj = lane & 15, lq = lane >> 4;
+    const int lj = lane & 15, lq = lane >> 4, lw = weight_row<HEAD>(lj);
     if constexpr (PREC == 0) {
         const float *As = static_cast<const float *>(As_);
         const float *Bs = static_cast<const float *>(Bs_);
@@ -285,7 +298,7 @@ __device__ __forceinline__ void chunk_mfma(const void *As_, const void *Bs_, f32
             for (int c4 = 0; c4 < CK / 4; ++c4) {
                 float b[NB];
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) b[nb] = Bs[(tap * CK + c4 * 4 + lq) * S::BS + nb * 16 + lj];
+                for (int nb = 0; nb < NB; ++nb) b[nb] = Bs[(tap * CK + c4 * 4 + lq) * S::BS + nb * 16 + lw];
 #pragma unroll
                 for (int i = 0; i < MB; ++i) {
                     const int blk = wave * MB + i, row = blk >> 1, cb = blk & 1;
@@ -311,7 +324,7 @@ __device__ __forceinline__ void chunk_mfma(const void *As_, const void *Bs_, f32
             i32x8 b[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                const unsigned char *bp = &Bs[(nb * 16 + lj) * S::BSK8 + s * 128 + lq * 32];
+                const unsigned char *bp = &Bs[(nb * 16 + lw) * S::BSK8 + s * 128 + lq * 32];
                 const uint4 u0 = *reinterpret_cast<const uint4 *>(bp);
                 const uint4 u1 = *reinterpret_cast<const uint4 *>(bp + 16);
                 b[nb] = i32x8{(int)u0.x, (int)u0.y, (int)u0.z, (int)u0.w,
@@ -345,7 +358,7 @@ __device__ __forceinline__ void chunk_mfma(const void *As_, const void *Bs_, f32
             bf16x8 b[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
-                b[nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8 *>(&Bs[(nb * 16 + lj) * S::BSK + k0]));
+                b[nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8 *>(&Bs[(nb * 16 + lw) * S::BSK + k0]));
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
                 const int blk = wave * MB + i, row = blk >> 1, cb = blk & 1;
@@ -377,7 +390,7 @@ __device__ __forceinline__ void chunk_mfma(const void *As_, const void *Bs_, f32
 // row partner is block i+2 of the same lane.
 // Per-lane output-channel constants of the epilogue: the bias and, for fp8,
 // the dequantisation factor of this lane's 4 channels in each block.
-template <int PREC, int NB>
+template <int PREC, int NB, bool HEAD>
 struct EpiConsts {
     float bias[NB][4], dq[NB][4];
     __device__ __forceinline__ void load(const ConvLayer &L, int g)
@@ -387,7 +400,7 @@ struct EpiConsts {
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int co = g * NB * 16 + nb * 16 + 4 * lq + v;
+                const int co = g * NB * 16 + nb * 16 + (HEAD ? 4 * v + lq : 4 * lq + v);
                 bias[nb][v] = co < L.Cout ? gload(L.bias + co) : 0.f;
                 dq[nb][v] = (PREC == 2 && co < L.Cout) ? gload(L.out_scale + co) : 1.f;
             }
@@ -397,7 +410,7 @@ struct EpiConsts {
 template <int PREC, int EPI, int TH, int NB, typename OutT>
 __device__ __forceinline__ void conv_epilogue(const ConvLayer &L, const FrameDesc &fd, int g, int x0,
                                               int y0, int Hl, int Wl, f32x4 (*acc)[NB],
-                                              const EpiConsts<PREC, NB> &ec)
+                                              const EpiConsts<PREC, NB, kHead<EPI>> &ec)
 {
     constexpr int MB = TH / 2;
     constexpr int NC = NB * 16;
@@ -412,11 +425,7 @@ __device__ __forceinline__ void conv_epilogue(const ConvLayer &L, const FrameDes
     const auto &bias = ec.bias;
     const auto &dq = ec.dq;
     float pe[CAN_POOL ? 2 : 1][CAN_POOL ? NB : 1][4];   // even-row partial sums
-    // head record: element offset of this lane's first channel plane, per block
     const size_t P = (size_t)Hl * Wl;
-    size_t plane0[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) plane0[nb] = (size_t)(g * NC + nb * 16 + 4 * lq) * P;
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
         const int blk = wave * MB + i, row = blk >> 1, cb = blk & 1;
@@ -427,21 +436,25 @@ __device__ __forceinline__ void conv_epilogue(const ConvLayer &L, const FrameDes
         uint2 pm[NB];   // packed 2x2 means of each block (odd rows, paired stores)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
+            if constexpr (kHead<EPI>) {
+                // head record (one block), planar [2M][H][W]: the 16 lanes of
+                // a channel write 16 consecutive pixels of its plane
+                OutT *q = dst + lq * P + (unsigned)(y * Wl + x);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (4 * k >= L.Cout) break;
+                    float v = acc[i][nb][k] * dq[nb][k] + bias[nb][k];
+                    if (4 * k < L.M) v = epilogue<EPI>(v, 4 * k + lq, L.M);
+                    if (in && 4 * k + lq < L.Cout) gstore(q + 4 * k * P, v);
+                }
+                continue;
+            }
             const int co = g * NC + nb * 16 + 4 * lq;
             const bool cin = co < L.Cout;
             float v[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = epilogue<EPI>(acc[i][nb][k] * dq[nb][k] + bias[nb][k], co + k, L.M);
-            if constexpr (EPI == EPI_HEAD_SOFTPLUS || EPI == EPI_HEAD_EXP) {
-                // head record, planar [2M][H][W]: the 16 lanes of a channel
-                // write 16 consecutive pixels of its plane
-                if (in) {
-                    OutT *q = dst + plane0[nb] + (unsigned)(y * Wl + x);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (co + k < L.Cout) gstore(q + k * P, v[k]);
-                }
-            } else if constexpr (std::is_same<OutT, float>::value) {
+            if constexpr (std::is_same<OutT, float>::value) {
                 // fp32 activations: Cout is a multiple of 16
                 if (in && cin) gstore(reinterpret_cast<gf32x4 *>(pp + co), gf32x4{v[0], v[1], v[2], v[3]});
             } else {
@@ -532,7 +545,7 @@ __global__ __launch_bounds__(kThreads, (MODE == CONV_PACK && PREC == 1 && KS == 
     st.init(L, g, x0, y0, Hl, Wl);
     const int nchunks = L.Cin_pad / CK;
     st.fetch(L, fd, s0, s1, 0, Wl);
-    EpiConsts<PREC, NB> ec;
+    EpiConsts<PREC, NB, kHead<EPI>> ec;
     if constexpr (MODE == CONV_PACK) {
         // the network input is one chunk: the epilogue's constants are
         // requested once the staged values are in LDS (their registers are
@@ -541,14 +554,14 @@ __global__ __launch_bounds__(kThreads, (MODE == CONV_PACK && PREC == 1 && KS == 
         st.commit(As, Bs, L.in_qscale);
         ec.load(L, g);
         lds_sync();
-        chunk_mfma<PREC, MODE, CK, TH, NB, SrcT, KS>(As, Bs, acc);
+        chunk_mfma<PREC, MODE, kHead<EPI>, CK, TH, NB, SrcT, KS>(As, Bs, acc);
     } else {
         for (int cc = 0; cc < nchunks; ++cc) {
             if (cc) __syncthreads();
             st.commit(As, Bs, L.in_qscale);
             __syncthreads();
             if (cc + 1 < nchunks) st.fetch(L, fd, s0, s1, cc + 1, Wl);
-            chunk_mfma<PREC, MODE, CK, TH, NB, SrcT, KS>(As, Bs, acc);
+            chunk_mfma<PREC, MODE, kHead<EPI>, CK, TH, NB, SrcT, KS>(As, Bs, acc);
         }
         ec.load(L, g);
     }
@@ -638,7 +651,8 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lj = lane & 15, lq = lane >> 4;
-    const int bq = lq ^ (((lj >> 2) & 1) << 1);   // swizzled weight column group
+    const int lw = weight_row<kHead<EPI>>(lj);
+    const int bq = lq ^ (((lw >> 2) & 1) << 1);   // swizzled weight column group
 
     const unsigned short *s0 =
         reinterpret_cast<const unsigned short *>(conv_src0(L, fd));
@@ -729,7 +743,7 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
                     b[nb] = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u16x8 *>(Bs + ((nb * 16 + lj) * BSK + s * 32 + bq * 8) * 2));
+                        bf16x8, *reinterpret_cast<const u16x8 *>(Bs + ((nb * 16 + lw) * BSK + s * 32 + bq * 8) * 2));
 #pragma unroll
                 for (int r = 0; r < HW; ++r)
 #pragma unroll
@@ -751,7 +765,7 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
         lds_barrier();   // the stage has been read before it is refilled
         if (cc + 1 < nchunks) issue(cc + 1, smem);
     }
-    EpiConsts<1, NB> ec;
+    EpiConsts<1, NB, kHead<EPI>> ec;
     ec.load(L, g);
     conv_epilogue<1, EPI, TH, NB, OutT>(L, fd, g, x0, y0, Hl, Wl, acc, ec);
 }

@@ -873,10 +873,26 @@ int conv_grid(const ConvLayer &L, int n, const int *H, const int *W)
 // 8 crops of 256x256 is 1 % slower at 1024 than here, 3 % at 2048.
 constexpr int kFp32Grid = 512;
 
+// Decoders of two or four blocks per group take 8-row tiles where enough of them
+// are left: each weight fragment read from LDS serves four blocks of 16 pixels
+// instead of two.  8 crops of 256x256: 96 -> 32 channels 264 -> 240 us, 160 -> 64
+// 198 -> 188.  The encoders, one block and three blocks measured slower so (registers:
+// one wave fewer per SIMD).
+static bool fp32_tall(const ConvLayer &L) { return L.ks == 3 && L.C1 > 0 && (L.NB == 2 || L.NB == 4); }
+
 int conv_fp32_tiles(ConvLayer &L, int n, const int *H, const int *W)
 {
     int blocks = conv_grid(L, n, H, W);
     const int nblk = L.Cout_pad / 16;
+    if (fp32_tall(L)) {
+        ConvLayer t = L;
+        t.th = 8;
+        const int b = conv_grid(t, n, H, W);
+        if (b >= kFp32Grid) {
+            L.th = 8;
+            return b;
+        }
+    }
     while (blocks < kFp32Grid && L.NB > 1) {
         do --L.NB;
         while (nblk % L.NB);
@@ -909,6 +925,13 @@ static void launch_one(const ConvLayer &L, const FrameArg &fa, int blocks, hipSt
 {
     using SrcT = typename std::conditional<PREC == 0, float, unsigned short>::type;
     constexpr int TH = MODE == CONV_PACK ? kTHP : PREC == 2 ? kTH8 : kTH;
+    if constexpr (PREC == 0 && MODE == CONV_CAT && (NB == 2 || NB == 4)) {
+        if (L.th == 8) {
+            hipLaunchKernelGGL((conv3x3_kernel<0, MODE, EPI, 8, CK, NB, float, float>), dim3(blocks), dim3(kThreads), 0,
+                               s, L, fa);
+            return;
+        }
+    }
     if constexpr (PREC == 0 && NB == 1) {
         if (launch_fp32_small<MODE, EPI, 2, CK>(L, fa, blocks, s)) return;
         if constexpr (TH == 8)

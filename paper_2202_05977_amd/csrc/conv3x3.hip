@@ -788,7 +788,7 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
 constexpr int kTH = WSKP_CONV_TH;
 // fp8: 8 rows, so that a weight fragment read from LDS serves four blocks of 16
 // pixels instead of two and the halo is a third instead of half of the tile; its time
-// goes to LDS reads and the quantisation while staging.  1080p, five levels:
+// goes to LDS reads and the quantisation while staging.  1080p, four levels:
 // 632 us with 4 rows, 557 with 8 (the full-resolution decoder 150 -> 127, the head
 // 94 -> 76, the widest decoder 105 -> 82).
 constexpr int kTH8 = 8;
@@ -869,7 +869,7 @@ int conv_grid(const ConvLayer &L, int n, const int *H, const int *W)
 // summation do not depend on the tiling.  The small net, us at 16x16 / 128x128 /
 // 256x256 / 320x400: 69 / 74 / 81 / 125 without the rule, 41 / 43 / 61 / 109 at
 // this line, 41 / 43 / 62 / 120 at 256 workgroups, 41 / 43 / 61 / 110 at 1024; the
-// 5-level net at 64x64 / 256x256: 235 / 270 -> 90 / 176.  A training step of
+// 4-level net at 64x64 / 256x256: 235 / 270 -> 90 / 176.  A training step of
 // 8 crops of 256x256 is 1 % slower at 1024 than here, 3 % at 2048.
 constexpr int kFp32Grid = 512;
 

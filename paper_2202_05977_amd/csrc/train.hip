@@ -13,7 +13,7 @@
 //   epilogue that writes the last contribution to an activation's gradient also
 //   applies that activation's ReLU mask, and the first contribution
 //   overwrites, so no input gradient is stored as such, no gradient buffer
-//   cleared and no mask pass run: a step of 8 crops of 256x256, 5 levels, took
+//   cleared and no mask pass run: a step of 8 crops of 256x256, 4 levels, took
 //   2477 us with an adjoint and a mask pass per conv and takes 2240.
 // The weight gradient's input is written out where it is computed (the
 // network input, a 2x2 mean); a decoder's, the [upsampled, skip]

@@ -152,13 +152,13 @@ static void *g_scratch_ptr[kMaxDevices];
 
 // FP32 3x3 convs: frames of at least this many pixels run the split kernel, in
 // denoising and in training alike (a frame's result depends neither on its
-// batch nor on who asks).  The split kernel is faster on small frames too
-// (128 x 128, three levels: 68 us against 80); they keep
-// v_mfma_f32_16x16x4f32 for the sake of training, whose crops are of 256 x 256
-// and less: a gradient is taken through the forward pass's ReLU masks, and any
-// change of the forward rounding carries a few pre-activations within it of
-// zero to the other side, which moves the gradient of a batch of such crops by
-// 2e-6 to 6e-5 of its norm.  720p is 7 times above the line.
+// batch nor on who asks): 720p, four levels, 985 us against 1460.  Smaller frames
+// keep v_mfma_f32_16x16x4f32.  The smallest are faster with it (128 x 128, three
+// levels: 47 us on cut tiles against 68), and training needs it, whose crops
+// are of 256 x 256 and less: a gradient is taken through the forward pass's ReLU
+// masks, and any change of the forward rounding carries a few pre-activations
+// within it of zero to the other side, which moves the gradient of a batch of
+// such crops by 2e-6 to 6e-5 of its norm.  720p is 7 times above the line.
 static constexpr long kSplitPixels = 1L << 17;
 
 static constexpr int kRingSlots = 8;

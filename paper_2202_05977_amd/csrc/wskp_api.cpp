@@ -1301,7 +1301,11 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
         else fa.table = tab;
         const std::vector<int> hv(nf, ops.H), wv(nf, ops.W);
         int blocks = conv_grid(c, nf, hv.data(), wv.data());
-        if (blocks < 512 && epi != EPI_BWD_CAT) {   // as in plan_convs
+        // 4-row tiles below two workgroups per CU, as in plan_convs; through the
+        // 2x2 mean below eight: that epilogue reads and writes four pixels for
+        // each of the conv's, and a single round of tall tiles leaves the memory idle
+        // meanwhile (8 crops, 64 -> 32 channels at 128x128: 111 us, 98 so)
+        if (blocks < (epi == EPI_BWD_POOL ? 2048 : 512) && epi != EPI_BWD_CAT) {
             c.th = 4;
             blocks = conv_grid(c, nf, hv.data(), wv.data());
         }

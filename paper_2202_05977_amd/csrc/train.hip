@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kTrThreads) void tr_pool_kernel(int H, int W, int C
 // interleaved head [P][2M] from the planar record [2M][P]; c = r/(a+eps_a),
 // mod = a + eps_a (the decode adjoint's inputs)
 // (whole records and pixels per store: one float per store, 8 M bytes apart
-// across lanes, took 36 us for 8 crops of 256x256)
+// across lanes, took 36 us for 8 crops of 256x256; now 14)
 template <int M>
 __global__ __launch_bounds__(kTrThreads) void tr_head_prep_kernel(long P, const float *planar, long sp, TrFrames fr,
                                                                    float eps_a, float *head, float *c, float *mod)

@@ -213,11 +213,12 @@ __global__ __launch_bounds__(kThreads, dir_min_wg(KS, R)) void conv_bf16_kernel(
     const int tr = wave * R * 3072;                    // a row: 2 KiB of pixels, 1 KiB of means
     // 16-byte group c of pixel p at group c ^ ((p >> 1) & 3): the 8 lanes of a
     // cycle hit distinct banks writing (8 pixels) and reading (2 pixels x 4)
-    auto put = [&](int at, int p, int q, const uint2 &a, const uint2 &b) {
+    auto put = [&](int at, int p, int q, const uint2 &a, const uint2 &b, bool on) {
         const auto sx = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
         const auto sy = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
-        *reinterpret_cast<gu32x4 *>(&smem[at + p * 64 + (((q + lh) ^ ((p >> 1) & 3)) << 4)]) =
-            gu32x4{sx[0], sy[0], sx[1], sy[1]};
+        if (on)
+            *reinterpret_cast<gu32x4 *>(&smem[at + p * 64 + (((q + lh) ^ ((p >> 1) & 3)) << 4)]) =
+                gu32x4{sx[0], sy[0], sx[1], sy[1]};
     };
     auto get = [&](int at, int p) {
         return *reinterpret_cast<const gu32x4 *>(&smem[at + p * 64 + (((lane & 3) ^ ((p >> 1) & 3)) << 4)]);
@@ -245,9 +246,11 @@ __global__ __launch_bounds__(kThreads, dir_min_wg(KS, R)) void conv_bf16_kernel(
         }
 #pragma unroll
         for (int q = 0; q < 4; q += 2) {
-            put(tr + r * 3072, lj, q, qs[q], qs[q + 1]);
-            // (both lanes of a column pair hold its mean and write the same)
-            if (POOL && r % 2) put(tr + r * 3072 + 2048, lj >> 1, q, pm[q], pm[q + 1]);
+            put(tr + r * 3072, lj, q, qs[q], qs[q + 1], true);
+            // the mean is the even lane's, which adds its pair's columns in order
+            // (the odd lane's sum of the odd row starts at the other column and
+            // may round differently)
+            if (POOL && r % 2) put(tr + r * 3072 + 2048, lj >> 1, q, pm[q], pm[q + 1], lj % 2 == 0);
         }
     }
     wait_lds();

@@ -76,3 +76,37 @@ def test_decoder_layers_against_oracle(cfg, sizes):
         assert rel_l2(y, ref) <= TOL_BF16 and max_rel(y, ref) <= TOL_BF16_MAX
     assert all(bool(torch.isfinite(f["out"]).all()) for f in frames)
     dn.close()
+
+
+@pytest.mark.parametrize("k", [3, 5])
+@pytest.mark.parametrize("block", [(1.0, 2.0 ** -8 - 2.0 ** -16, 2.0 ** -16 - 2.0 ** -24, 1.5 * 2.0 ** -24),
+                                   (1.0, 2.0 ** -8 - 2.0 ** -16, 1.5 * 2.0 ** -24, 2.0 ** -16 - 2.0 ** -24)])
+def test_pooled_means_add_in_order(block, k):
+    """Blocks whose sum is a bf16 tie's upper or lower side depending on which value
+    of the second row is added first: level 1's means are of the sums in the order
+    (0,0), (0,1), (1,0), (1,1).  Both encoders copy the albedo's first channel."""
+    from paper_2202_05977_amd import wskp
+    cfg = synth.NetConfig(levels=3, channels=(32, 32, 32), kernel_sizes=(3,), conv_size=k)
+    parts = []
+    for name, ci, co in synth.conv_shapes(cfg):
+        w = np.zeros((co, ci, k, k), np.float32)
+        if name == "enc0":
+            w[:, 3, k // 2, k // 2] = 1.0
+        elif name == "enc1":
+            w[np.arange(32), np.arange(32), k // 2, k // 2] = 1.0
+        parts += [w.ravel(), np.zeros(co, np.float32)]
+    dn = wskp.Denoiser(cfg, np.concatenate(parts), "bf16")
+    H, W = 24, 152
+    fr = synth.make_frame(3, H, W)
+    v = np.tile(np.array(block, np.float32).reshape(2, 2), (H // 4, W // 4))     # level 1's map
+    fr["albedo"][:] = np.repeat(np.repeat(v, 2, 0), 2, 1)[..., None]
+    dn(to_dev(fr))
+    e1 = dn.intermediate([H], [W], 0, 1).float().cpu()
+    assert torch.equal(e1, torch.from_numpy(v)[..., None].expand_as(e1))
+    s = np.float32(block[0])
+    for b in block[1:]:
+        s = np.float32(s + np.float32(b))
+    mean = torch.tensor(0.25 * s, dtype=torch.float32).bfloat16()
+    p1 = dn.intermediate([H], [W], 0, 301).cpu()
+    assert torch.equal(p1, mean.expand_as(p1))
+    dn.close()

@@ -30,6 +30,53 @@ __device__ __forceinline__ unsigned cvt_pk_bf16(float a, float b)
 
 __device__ __forceinline__ unsigned short f32_to_bf16(float f) { return (unsigned short)cvt_pk_bf16(f, 0.f); }
 
+// Three bf16 parts of two values, packed (the first value in the low half):
+// v = p0 + p1 + p2, each part the round-to-nearest bf16 of what the parts before
+// it leave.  Exact from 2^-110 up (below, the third and then the second part
+// runs out of bf16's range).  Infinities and NaNs stay in their first part
+// and make the others NaN (see sum_parts).  Finite values above the largest bf16
+// would round to infinity: WIDE gives them that for their first part.
+constexpr float kBf16Max = 0x1.fep127f;
+template <bool WIDE>
+__device__ __forceinline__ void split_bf16(float a, float b, unsigned (&p)[3])
+{
+    auto first = [](float v) {
+        return WIDE && fabsf(v) < INFINITY ? __builtin_amdgcn_fmed3f(v, -kBf16Max, kBf16Max) : v;
+    };
+    p[0] = cvt_pk_bf16(first(a), first(b));
+    a -= __uint_as_float(p[0] << 16);
+    b -= __uint_as_float(p[0] & 0xffff0000u);
+    p[1] = cvt_pk_bf16(a, b);
+    a -= __uint_as_float(p[1] << 16);
+    b -= __uint_as_float(p[1] & 0xffff0000u);
+    p[2] = cvt_pk_bf16(a, b);
+}
+// 2 N values; the wide form only where a lane of the wave has a value that needs it
+// (a maximum over three costs half an instruction a value, the wide form three)
+template <int N>
+__device__ __forceinline__ void split_bf16_run(const float *v, unsigned (&p)[N][3])
+{
+    float m = 0.f;
+#pragma unroll
+    for (int e = 0; e < 2 * N; ++e) m = fmaxf(m, fabsf(v[e]));
+    if (__builtin_expect(__any(m > kBf16Max), 0)) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) split_bf16<true>(v[2 * e], v[2 * e + 1], p[e]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; ++e) split_bf16<false>(v[2 * e], v[2 * e + 1], p[e]);
+    }
+}
+// The sum of a product of split operands from its main accumulator (the
+// products of the first parts) and that of the small terms.  Where an
+// operand is infinite the small terms are NaN and the main sum is the fp32 one:
+// infinite, or NaN for infinities of both signs or times zero.
+__device__ __forceinline__ float sum_parts(float main, float small)
+{
+    const float v = main + small;
+    return v == v ? v : main;
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     __device__ static __forceinline__ void load4(const float *p, float v[4])

@@ -1,7 +1,6 @@
 // FP32 3x3 convolutions on the bf16 matrix cores: every fp32 operand is
-// split exactly into three bf16 parts, x = x0 + x1 + x2 (each part the
-// round-to-nearest bf16 of what the parts before it leave), and a product
-// is the sum of the six part products above 2^-25 of it:
+// split into three bf16 parts, x = x0 + x1 + x2 (split_bf16; exact from 2^-110
+// up), and a product is the sum of the six part products above 2^-25 of it:
 //   x w = x0 w0 + (x1 w0 + x0 w1) + (x1 w1 + x2 w0 + x0 w2) + O(2^-25)
 // Part products are exact in the MFMA, which accumulates in fp32.  x0 w0 goes
 // into one accumulator and the five small terms into another; the two are
@@ -19,7 +18,7 @@
 // A workgroup of 4 waves owns a tile of 4 HW x 32 output pixels and 32 output
 // channels; a wave owns HW rows.  Per chunk of 16 input channels the halo is
 // loaded as fp32 (one chunk ahead, in registers), split and written to LDS as
-// three planes of bf16, with the chunk's weights (split on the host) beside
+// three planes of bf16, with the chunk's weights (split when packed) beside
 // it.  16 channels: at HW = 2 the stage is 59 KiB, so two workgroups fit a CU
 // and one's staging hides behind the other's MFMAs; 32 would leave one.  The
 // chunk is one k-step of the 32x32x16 form, and for one column offset dx a
@@ -31,10 +30,8 @@
 // 32x32x16 MFMAs on random data from registers at 1830 (1.83 GHz: the clock
 // gives way).
 //
-// Infinities and NaNs: a part product of an infinite value with a part of
-// the other sign gives NaN where the fp32 sum has an infinity, so outputs that
-// end as NaN (rare, whatever the input) are evaluated again with plain fp32
-// multiply-adds.
+// Infinities and NaNs come out as in a plain fp32 sum (sum_parts), at no cost:
+// the sums of an output with a NaN among its operands are as long as any.
 #include "conv_device.h"
 
 namespace wskp {
@@ -45,46 +42,6 @@ typedef unsigned int u32v4 __attribute__((ext_vector_type(4)));
 constexpr int kSpCK = 16;                       // input channels per chunk
 constexpr int kSpFrag = 1024;                   // bytes of one weight fragment (32 channels x 16)
 constexpr int kSpWFrags = 9 * 3;                // fragments per chunk and 32 output channels
-
-// Three bf16 parts of a pair of values, packed (first value in the low half).
-__device__ __forceinline__ void split2(float a, float b, unsigned &p0, unsigned &p1, unsigned &p2)
-{
-    p0 = cvt_pk_bf16(a, b);
-    a -= __uint_as_float(p0 << 16);
-    b -= __uint_as_float(p0 & 0xffff0000u);
-    p1 = cvt_pk_bf16(a, b);
-    a -= __uint_as_float(p1 << 16);
-    b -= __uint_as_float(p1 & 0xffff0000u);
-    p2 = cvt_pk_bf16(a, b);
-}
-
-// One input value of the layer (virtual channel c at (y, x) of the output's
-// level; 0 outside the image): only for the NaN outputs.
-template <int MODE>
-__device__ float split_input(const ConvLayer &L, const FrameDesc &fd, const float *s0, const float *s1, int c, int y,
-                             int x, int Hl, int Wl)
-{
-    if (y < 0 || y >= Hl || x < 0 || x >= Wl) return 0.f;
-    if constexpr (MODE == CONV_PACK) {
-        if (c >= 10) return 0.f;
-        float v[10];
-        pack_load(fd, (size_t)y * Wl + x, v);
-        pack_transform(L, v);
-        float r = v[0];
-#pragma unroll
-        for (int i = 1; i < 10; ++i) r = c == i ? v[i] : r;
-        return r;
-    } else if constexpr (MODE == CONV_POOL) {
-        const float *b = s0 + ((size_t)(2 * y) * (2 * Wl) + 2 * x) * L.C0 + c;
-        const size_t rs = (size_t)(2 * Wl) * L.C0;
-        return 0.25f * (gload(b) + gload(b + L.C0) + gload(b + rs) + gload(b + rs + L.C0));
-    } else if constexpr (MODE == CONV_CAT) {
-        if (c < L.C0) return gload(s0 + ((size_t)(y >> 1) * (Wl >> 1) + (x >> 1)) * L.C0 + c);
-        return gload(s1 + ((size_t)y * Wl + x) * L.C1 + (c - L.C0));
-    } else {
-        return gload(s0 + ((size_t)y * Wl + x) * L.C0 + c);
-    }
-}
 
 // Epilogues of the input gradients in training: what the gradient gm of the
 // layer's input becomes is written at once, so it is itself never stored.
@@ -277,22 +234,20 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_split_kernel(ConvLayer L,
                 for (int e = 0; e < 16; ++e) x[e] = e < 10 && ((live >> k) & 1u) ? in[k][e < 10 ? e : 0] : 0.f;
 #pragma unroll
                 for (int cg = 0; cg < 2; ++cg) {
-                    unsigned p[3][4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) split2(x[cg * 8 + 2 * e], x[cg * 8 + 2 * e + 1], p[0][e], p[1][e], p[2][e]);
+                    unsigned p[4][3];
+                    split_bf16_run(x + cg * 8, p);
 #pragma unroll
                     for (int q = 0; q < 3; ++q)
                         *reinterpret_cast<uint4 *>(&smem[q * PART + (dst[k] ^ (cg << 4))]) =
-                            make_uint4(p[q][0], p[q][1], p[q][2], p[q][3]);
+                            make_uint4(p[0][q], p[1][q], p[2][q], p[3][q]);
                 }
             } else {
-                unsigned p[3][4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) split2(in[k][2 * e], in[k][2 * e + 1], p[0][e], p[1][e], p[2][e]);
+                unsigned p[4][3];
+                split_bf16_run(in[k], p);
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
                     *reinterpret_cast<uint4 *>(&smem[q * PART + dst[k]]) =
-                        make_uint4(p[q][0], p[q][1], p[q][2], p[q][3]);
+                        make_uint4(p[0][q], p[1][q], p[2][q], p[3][q]);
             }
         }
 #pragma unroll
@@ -372,44 +327,10 @@ __global__ __launch_bounds__(kThreads, 2) void conv3x3_split_kernel(ConvLayer L,
     // ---- epilogue: lane (j, h) holds pixel j of its rows, channels
     // 8 q + 4 h .. + 3 for q = 0..3
     const int co0 = g * 32 + 4 * lh;
-    bool nan = false;
 #pragma unroll
-    for (int r = 0; r < HW; ++r) {
-        acc[r] += sml[r];
-        const bool in = y0 + wave * HW + r < Hl && x0 + lj < Wl;
+    for (int r = 0; r < HW; ++r)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) nan |= in && !(acc[r][i] == acc[r][i]);
-    }
-    if (__syncthreads_or(nan)) {
-        float *v = reinterpret_cast<float *>(smem) + tid;
-        static_assert(HW * 16 * kThreads * 4 <= A_BYTES + W_BYTES, "values of the workgroup fit the stage");
-#pragma unroll
-        for (int r = 0; r < HW; ++r)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) v[(r * 16 + i) * kThreads] = acc[r][i];
-#pragma unroll 1
-        for (int e = 0; e < HW * 16; ++e) {
-            const float a = v[e * kThreads];
-            const int y = y0 + wave * HW + (e >> 4), x = x0 + lj, c8 = (e >> 2) & 3;
-            const int l32 = 8 * c8 + 4 * lh + (e & 3);   // channel within the 32
-            if (a == a || y >= Hl || x >= Wl) continue;
-            float s = 0.f;
-#pragma unroll 1
-            for (int k = 0; k < nch * 9 * kSpCK; ++k) {
-                const int c = k % kSpCK, t = k / kSpCK % 9, cc = k / (kSpCK * 9);
-                const unsigned short *wp = reinterpret_cast<const unsigned short *>(wsrc + (size_t)cc * W_BYTES) +
-                                           t * 3 * (kSpFrag / 2) + ((c >> 3) * 32 + l32) * 8 + (c & 7);
-                const float wv = (bf16_to_f32(gload(wp)) + bf16_to_f32(gload(wp + kSpFrag / 2))) +
-                                 bf16_to_f32(gload(wp + kSpFrag));
-                s = fmaf(split_input<MODE>(L, fd, s0, s1, cc * kSpCK + c, y + t / 3 - 1, x + t % 3 - 1, Hl, Wl), wv, s);
-            }
-            v[e * kThreads] = s;
-        }
-#pragma unroll
-        for (int r = 0; r < HW; ++r)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[r][i] = v[(r * 16 + i) * kThreads];
-    }
+        for (int i = 0; i < 16; ++i) acc[r][i] = sum_parts(acc[r][i], sml[r][i]);
     if constexpr (EPI == EPI_BWD_MASK || EPI == EPI_BWD_CAT || EPI == EPI_BWD_POOL) {
         bwd_epilogue<EPI, HW>(L, fd, acc, co0, y0 + wave * HW, x0 + lj, Hl, Wl);
         return;
@@ -486,12 +407,10 @@ __global__ __launch_bounds__(kThreads) void conv_pack_kernel(PackJobs jobs)
         v = gload(p.kind == PACK_SPLIT_DGRAD ? p.w + ((size_t)ci * p.Co + co) * 9 + (8 - t)
                                              : p.w + ((size_t)co * p.Ci + ci) * 9 + t);
     unsigned short *o = static_cast<unsigned short *>(p.out) + ((size_t)((gr * p.nch + cc) * 9 + t) * 3) * 512 + lane * 8 + e;
+    unsigned parts[3];
+    split_bf16<true>(v, 0.f, parts);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const unsigned short h = f32_to_bf16(v);
-        gstore(o + q * 512, h);
-        v -= bf16_to_f32(h);
-    }
+    for (int q = 0; q < 3; ++q) gstore(o + q * 512, (unsigned short)parts[q]);
 }
 
 void PackJobs::add_split(int Ci, int Co, bool dgrad, const float *w, void *out)

@@ -1,10 +1,12 @@
 // Weight gradients of the training step on the bf16 matrix cores:
 //   dw[co][ci][tap] = sum_p gm[p][co] in[p + off(tap)][ci],  db[co] = sum_p gm[p][co]
 // (3x3, zero padding, NHWC fp32), a GEMM over pixels.  Every fp32 operand is
-// taken as the exact sum of three bf16 parts and a product as its six largest
-// part products, the five small ones in an accumulator of their own
+// taken as the sum of three bf16 parts (split_bf16) and a product as its six
+// largest part products, the five small ones in an accumulator of their own
 // (conv_split.hip: closer to float64 than v_mfma_f32_16x16x4f32, at 2.7 times
-// its rate).
+// its rate).  Strips with infinite or very large operands are summed again by a
+// careful pass (see there), which costs the others nothing: a step of 8 crops of
+// 256x256 takes 2166 us without it and 2170 with it, the runs' spread.
 //
 // A workgroup of 4 waves owns 32 output x 32 input channels, a wave 16 x 16
 // with all 9 taps (v_mfma_f32_16x16x32_bf16, 32 pixels of an image row per
@@ -34,18 +36,6 @@ constexpr int kWsIn = 112, kWsGm = 80;    // bytes per channel of an LDS row: 48
 constexpr int kWsInRow = 3 * 32 * kWsIn, kWsGmRow = 3 * 32 * kWsGm;
 constexpr unsigned kWsOut = 0x80000000u;  // beyond every buffer (maps stay below 2 GiB): loads read zeros
 
-// Three packed bf16 parts of two values (first in the low half).
-__device__ __forceinline__ void wg_split2(float a, float b, unsigned (&p)[3])
-{
-    p[0] = cvt_pk_bf16(a, b);
-    a -= __uint_as_float(p[0] << 16);
-    b -= __uint_as_float(p[0] & 0xffff0000u);
-    p[1] = cvt_pk_bf16(a, b);
-    a -= __uint_as_float(p[1] << 16);
-    b -= __uint_as_float(p[1] & 0xffff0000u);
-    p[2] = cvt_pk_bf16(a, b);
-}
-
 // VEC: the input's channel counts are multiples of 4 (else the network input's
 // 10: one load per channel).
 template <bool VEC>
@@ -55,6 +45,7 @@ __global__ __launch_bounds__(256, 2) void tr_wgrad_split_kernel(int H, int W, in
                                                                 long sup, int Cu, float *part, float *partb)
 {
     __shared__ __attribute__((aligned(16))) unsigned char smem[2][kWsInRow + kWsGmRow];
+    __shared__ int again;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lj = lane & 15, lq = lane >> 4;
     const int co0 = blockIdx.y * 32, ci0 = blockIdx.z * 32, Ci = Cu + Cf;
@@ -128,12 +119,12 @@ __global__ __launch_bounds__(256, 2) void tr_wgrad_split_kernel(int H, int W, in
             }
         }
     };
-    auto put_item = [&](const Item &it, int buf, const float (&v)[2][4]) {
+    auto put_item = [&](auto careful, const Item &it, int buf, const float (&v)[2][4]) {
         const int stride = it.is_in ? kWsIn : kWsGm, part_b = it.is_in ? 32 * kWsIn : 32 * kWsGm;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             unsigned p[3];
-            wg_split2(v[0][e], v[1][e], p);
+            split_bf16<careful()>(v[0][e], v[1][e], p);
 #pragma unroll
             for (int q = 0; q < 3; ++q)
                 *reinterpret_cast<unsigned *>(&smem[buf][it.dst + q * part_b + e * stride]) = p[q];
@@ -144,9 +135,9 @@ __global__ __launch_bounds__(256, 2) void tr_wgrad_split_kernel(int H, int W, in
         load_item(ia, (ia.is_in ? ya - 1 : ya) + s, va);
         if (wave == 0) load_item(ib, ya - 1 + s, vb);
     };
-    auto commit = [&](int buf) {
-        put_item(ia, buf, va);
-        if (tid < 16) put_item(ib, buf, vb);
+    auto commit = [&](auto careful, int buf) {
+        put_item(careful, ia, buf, va);
+        if (tid < 16) put_item(careful, ib, buf, vb);
     };
 
     // ---- accumulators of 16 co x 16 ci: main and small terms of each tap, and
@@ -155,71 +146,127 @@ __global__ __launch_bounds__(256, 2) void tr_wgrad_split_kernel(int H, int W, in
     const bool bias = blockIdx.z == 0 && cih == 0;
     // (a 16 x 16 block past the layer's channels: its wave only stages)
     const bool live = co0 + coh * 16 < Co && ci0 + cih * 16 < Ci;
-    f32x4 acc[9], sml[9], bm = {0.f, 0.f, 0.f, 0.f}, bs = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = sml[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[9], sml[9], bm, bs;
     // gradient fragments of rows y + 1, y, y - 1 of the current input row y
     bf16x8 g[3][3];
+    auto clear = [&]() {
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
+        for (int t = 0; t < 9; ++t) acc[t] = sml[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bm = bs = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < 3; ++q) g[r][q] = __builtin_bit_cast(bf16x8, u16x8{0, 0, 0, 0, 0, 0, 0, 0});
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) g[r][q] = __builtin_bit_cast(bf16x8, u16x8{0, 0, 0, 0, 0, 0, 0, 0});
+    };
+    clear();
     const bf16x8 one = __builtin_bit_cast(
         bf16x8, u16x8{0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80});
 
+    // One pass over the strip.  The careful one takes the wide split, and only rows and
+    // columns of the image: elsewhere the gradient is zero, and zero times an
+    // infinity or a NaN is NaN.
     const int steps = yb - ya + 2;   // input rows ya - 1 .. yb
-    fetch(0);
-    commit(0);
-    fetch(1);
-    lds_sync();
-    for (int s = 0; s < steps; ++s) {
-        const int buf = s & 1;
-        const unsigned char *row = smem[buf];
-        if (s + 1 < steps) commit(buf ^ 1);   // its loads were issued a step ago
-        if (s + 2 < steps) fetch(s + 2);
-        if (!live) {
-            lds_sync();
-            continue;
-        }
-        // rows roll: g[2] = row y - 1, g[1] = row y, g[0] = row y + 1 (new)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            g[2][q] = g[1][q];
-            g[1][q] = g[0][q];
-            g[0][q] = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const gu32x4 *>(&row[kWsInRow + (q * 32 + coh * 16 + lj) * kWsGm + lq * 16]));
-        }
-        bf16x8 x[3][3];   // [part][dx]
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const unsigned char *b = &row[(q * 32 + cih * 16 + lj) * kWsIn + 16 + lq * 16];
-            const gu32x4 c = *reinterpret_cast<const gu32x4 *>(b);
-            const unsigned pv = *reinterpret_cast<const unsigned *>(b - 4), nx = *reinterpret_cast<const unsigned *>(b + 16);
-            const unsigned s0 = __builtin_amdgcn_alignbit(c[0], pv, 16), s1 = __builtin_amdgcn_alignbit(c[1], c[0], 16);
-            const unsigned s2 = __builtin_amdgcn_alignbit(c[2], c[1], 16), s3 = __builtin_amdgcn_alignbit(c[3], c[2], 16);
-            const unsigned s4 = __builtin_amdgcn_alignbit(nx, c[3], 16);
-            x[q][0] = __builtin_bit_cast(bf16x8, gu32x4{s0, s1, s2, s3});
-            x[q][1] = __builtin_bit_cast(bf16x8, c);
-            x[q][2] = __builtin_bit_cast(bf16x8, gu32x4{s1, s2, s3, s4});
-        }
-        // tap (dy, dx) of gradient row y - dy + 1
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            // (gradient part, input part): the smallest products first
-            const int gq = k == 0 ? 2 : k == 1 ? 0 : k == 2 ? 1 : k == 3 ? 1 : 0;
-            const int xq = k == 0 ? 0 : k == 1 ? 2 : k == 2 ? 1 : k == 3 ? 0 : k == 4 ? 1 : 0;
-#pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                f32x4 &d = k < 5 ? sml[t] : acc[t];
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[t / 3][gq], x[xq][t % 3], d, 0, 0, 0);
-            }
-        }
-        if (bias) {
-            bs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[0][2], one, bs, 0, 0, 0);
-            bs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[0][1], one, bs, 0, 0, 0);
-            bm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[0][0], one, bm, 0, 0, 0);
-        }
+    auto strip = [&](auto careful) {
+        // (dx = 0) the input beside column W, the image's last, in this lane's dword i
+        auto past = [&](int i) {
+            const int d = W - x0 - (lq * 8 + 2 * i);
+            return d == 0 ? 0xffff0000u : d == 1 ? 0x0000ffffu : 0xffffffffu;
+        };
+        fetch(0);
+        commit(careful, 0);
+        fetch(1);
         lds_sync();
+        for (int s = 0; s < steps; ++s) {
+            const int buf = s & 1;
+            const unsigned char *row = smem[buf];
+            if (s + 1 < steps) commit(careful, buf ^ 1);   // its loads were issued a step ago
+            if (s + 2 < steps) fetch(s + 2);
+            if (!live) {
+                lds_sync();
+                continue;
+            }
+            // rows roll: g[2] = row y - 1, g[1] = row y, g[0] = row y + 1 (new)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                g[2][q] = g[1][q];
+                g[1][q] = g[0][q];
+                g[0][q] = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const gu32x4 *>(&row[kWsInRow + (q * 32 + coh * 16 + lj) * kWsGm + lq * 16]));
+            }
+            bf16x8 x[3][3];   // [part][dx]
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const unsigned char *b = &row[(q * 32 + cih * 16 + lj) * kWsIn + 16 + lq * 16];
+                const gu32x4 c = *reinterpret_cast<const gu32x4 *>(b);
+                const unsigned pv = *reinterpret_cast<const unsigned *>(b - 4), nx = *reinterpret_cast<const unsigned *>(b + 16);
+                unsigned s0 = __builtin_amdgcn_alignbit(c[0], pv, 16), s1 = __builtin_amdgcn_alignbit(c[1], c[0], 16);
+                unsigned s2 = __builtin_amdgcn_alignbit(c[2], c[1], 16), s3 = __builtin_amdgcn_alignbit(c[3], c[2], 16);
+                const unsigned s4 = __builtin_amdgcn_alignbit(nx, c[3], 16);
+                x[q][2] = __builtin_bit_cast(bf16x8, gu32x4{s1, s2, s3, s4});
+                if constexpr (careful()) {
+                    s0 &= past(0);
+                    s1 &= past(1);
+                    s2 &= past(2);
+                    s3 &= past(3);
+                }
+                x[q][0] = __builtin_bit_cast(bf16x8, gu32x4{s0, s1, s2, s3});
+                x[q][1] = __builtin_bit_cast(bf16x8, c);
+            }
+            // tap (dy, dx) of gradient row y - dy + 1
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                // (gradient part, input part): the smallest products first
+                const int gq = k == 0 ? 2 : k == 1 ? 0 : k == 2 ? 1 : k == 3 ? 1 : 0;
+                const int xq = k == 0 ? 0 : k == 1 ? 2 : k == 2 ? 1 : k == 3 ? 0 : k == 4 ? 1 : 0;
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    if (careful() && (s < t / 3 || s - t / 3 >= yb - ya)) continue;
+                    f32x4 &d = k < 5 ? sml[t] : acc[t];
+                    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[t / 3][gq], x[xq][t % 3], d, 0, 0, 0);
+                }
+            }
+            if (bias) {
+                bs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[0][2], one, bs, 0, 0, 0);
+                bs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[0][1], one, bs, 0, 0, 0);
+                bm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g[0][0], one, bm, 0, 0, 0);
+            }
+            lds_sync();
+        }
+    };
+    if (tid == 0) again = 0;
+    strip(std::false_type{});
+    // A NaN among the sums is an operand's, or came of an infinite or very large
+    // operand: if the strip has one, it is summed again.
+    float z = 0.f;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z += acc[t][r] + sml[t][r];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z += bm[r] + bs[r];
+    if (z != z) again = 1;
+    lds_sync();
+    if (__builtin_amdgcn_readfirstlane(again)) {
+        float big = 0.f;
+        auto note = [&](const Item &it, const float (&v)[2][4]) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    big = fmaxf(big, fabsf(v[p][e]));
+                    // (maps other than the network's input hold no NaN: the ReLU drops them)
+                    if (!VEC && it.is_in && v[p][e] != v[p][e]) big = INFINITY;
+                }
+        };
+        for (int s = 0; s < steps; ++s) {
+            fetch(s);
+            note(ia, va);
+            if (tid < 16) note(ib, vb);
+        }
+        if (__syncthreads_or(big > kBf16Max)) {
+            clear();
+            strip(std::true_type{});
+        }
     }
     // lane (q, j) holds rows 4 q + r (output channel), column j (input channel)
     if (!live) return;
@@ -232,10 +279,10 @@ __global__ __launch_bounds__(256, 2) void tr_wgrad_split_kernel(int H, int W, in
         if (ci < Ci) {
             float v[9];
 #pragma unroll
-            for (int t = 0; t < 9; ++t) v[t] = acc[t][r] + sml[t][r];
+            for (int t = 0; t < 9; ++t) v[t] = sum_parts(acc[t][r], sml[t][r]);
             store_floats<9>(part + base + ((long)co * Ci + ci) * 9, v);
         }
-        if (bias && lj == 0) gstore(partb + (long)blockIdx.x * Co + co, bm[r] + bs[r]);
+        if (bias && lj == 0) gstore(partb + (long)blockIdx.x * Co + co, sum_parts(bm[r], bs[r]));
     }
 }
 

@@ -58,3 +58,54 @@ def test_weight_gradients_against_oracle(cfg, sizes):
             assert not a.any(), name
         off += n
     dn.close()
+
+
+ONE = synth.NetConfig(levels=1, channels=(16,), kernel_sizes=(3, 5))
+
+
+def _grads(cfg, blob, fr):
+    from paper_2202_05977_amd import wskp
+    H, W = fr["depth"].shape[:2]
+    dn = wskp.Denoiser(cfg, blob, "fp32")
+    f = to_dev(fr)
+    f["out"] = torch.empty_like(f["radiance"])
+    grad, loss = torch.empty(blob.size, device="cuda"), torch.empty(1, device="cuda")
+    ws = torch.empty(wskp.wskp_train_workspace_size(dn.h, [H], [W]), dtype=torch.uint8, device="cuda")
+    wskp.wskp_train_grads(dn.h, [f], [f["clean"]], grad, loss, ws)
+    g = grad.cpu().numpy().astype(np.float64)
+    dn.close()
+    return g, oracle.train_grads(fr, fr["clean"], blob, cfg)[1]
+
+
+def test_activations_beyond_the_largest_bf16():
+    """A channel of 0 and 3.4e38, which would round to infinity in bf16: the head's
+    gradient for it, and for the others, is finite and the oracle's."""
+    blob = synth.make_weights(ONE, 4)
+    w0, head = blob[:1440].reshape(16, 10, 3, 3), blob[1456:-4].reshape(4, 16, 3, 3)
+    w0[0] = 0
+    w0[0, 9, 1, 1] = 3.4e38
+    blob[1440] = 0
+    head[:, 0] = 0
+    head[:, 0, 1, 1] = np.array([1, -1, 1, -1]) * 2.0 ** -125
+    fr = synth.make_frame(5, 40, 70)
+    fr["depth"][:] = np.where(fr["depth"] < np.median(fr["depth"]), 1.0, 10.0)
+    g, ref = (v[1456:-4].reshape(4, 16, 9) for v in _grads(ONE, blob, fr))
+    assert np.all(np.isfinite(g))
+    assert rel_l2(g[:, 0], ref[:, 0]) <= TOL_GRAD and rel_l2(g[:, 1:], ref[:, 1:]) <= TOL_GRAD
+
+
+@pytest.mark.parametrize("y,x", [(0, 0), (32, 44)])
+def test_infinite_input_in_a_corner(y, x):
+    """An infinite input where every activation that sees it is zero: the taps that
+    pair it with such an activation are zero times infinity, the taps that would
+    pair it with a pixel outside the image are the oracle's.  (32, 44): the last
+    row of its strip and a column within one."""
+    blob = synth.make_weights(ONE, 4)
+    w0 = blob[:1440].reshape(16, 10, 3, 3)
+    w0[:, 6] = -np.abs(w0[:, 6])
+    fr = synth.make_frame(5, 33, 45)
+    fr["normal"][y, x, 0] = np.inf
+    g, ref = (v[:1440].reshape(16, 10, 9) for v in _grads(ONE, blob, fr))
+    assert np.array_equal(np.isnan(g), np.isnan(ref)) and np.isnan(ref).sum() == 16 * 4
+    fin = np.isfinite(ref)
+    assert fin.sum() == 16 * 86 and rel_l2(g[fin], ref[fin]) <= TOL_GRAD

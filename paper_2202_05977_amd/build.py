@@ -16,7 +16,7 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed-fp32 instructions are kept out of all device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function",
+    "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function", "-Werror=align-mismatch",
 ]
 
 

@@ -39,19 +39,20 @@ __device__ __forceinline__ void gstore(T *p, T v)
     *(__attribute__((address_space(1))) T *)p = v;
 }
 // N consecutive floats from an address of any float alignment, in the widest
-// loads that N allows (the hardware takes them at 4-byte alignment).
+// loads that N allows (the hardware takes them at 4-byte alignment, which the
+// types state: gload and gstore would deduce the types' natural alignment).
 typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float uf2 __attribute__((ext_vector_type(2), aligned(4)));
 template <int N>
 __device__ __forceinline__ void load_floats(const float *p, float *v)
 {
     if constexpr (N >= 4) {
-        const uf4 q = gload(reinterpret_cast<const uf4 *>(p));
+        const uf4 q = *(const __attribute__((address_space(1))) uf4 *)p;
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = q[i];
         if constexpr (N > 4) load_floats<N - 4>(p + 4, v + 4);
     } else if constexpr (N >= 2) {
-        const uf2 q = gload(reinterpret_cast<const uf2 *>(p));
+        const uf2 q = *(const __attribute__((address_space(1))) uf2 *)p;
         v[0] = q[0];
         v[1] = q[1];
         if constexpr (N > 2) load_floats<N - 2>(p + 2, v + 2);
@@ -63,10 +64,10 @@ template <int N>
 __device__ __forceinline__ void store_floats(float *p, const float *v)
 {
     if constexpr (N >= 4) {
-        gstore(reinterpret_cast<uf4 *>(p), uf4{v[0], v[1], v[2], v[3]});
+        *(__attribute__((address_space(1))) uf4 *)p = uf4{v[0], v[1], v[2], v[3]};
         if constexpr (N > 4) store_floats<N - 4>(p + 4, v + 4);
     } else if constexpr (N >= 2) {
-        gstore(reinterpret_cast<uf2 *>(p), uf2{v[0], v[1]});
+        *(__attribute__((address_space(1))) uf2 *)p = uf2{v[0], v[1]};
         if constexpr (N > 2) store_floats<N - 2>(p + 2, v + 2);
     } else if constexpr (N == 1) {
         gstore(p, v[0]);

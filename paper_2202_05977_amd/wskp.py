@@ -151,13 +151,16 @@ def _ptr(t: Optional[torch.Tensor], name: str, shape: Optional[Sequence[int]] = 
     return ctypes.c_void_p(t.data_ptr())
 
 
+# the current stream's handle without a Stream object (torch's own, private name):
+# building one takes 3 us, and 15 us on autograd's thread
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> ctypes.c_void_p:
     if stream is None:
-        # the current stream's handle without a Stream object: building one takes
-        # 3 us, and 15 us on autograd's thread
-        if not torch.cuda.is_initialized():
-            torch.cuda.init()
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+        if _raw_stream is not None:
+            return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 

@@ -190,3 +190,18 @@ def test_repvgg_merge_rejects_bad_arguments():
     st = wskp.lib().wskp_repvgg_merge(2, 2, None, None, w.ctypes.data, None, None, None, 0,
                                       out_w.ctypes.data, out_b.ctypes.data)
     assert st == -1
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream_with_and_without_torchs_private_handle(monkeypatch, private):
+    """Without a stream argument a call runs on the current device's current stream, also
+    where torch has no function that returns its handle alone."""
+    wskp, torch = _wskp(), pytest.importorskip("torch")
+
+    class Stream:
+        cuda_stream = 0x1234
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    monkeypatch.setattr(wskp, "_raw_stream", (lambda d: 0x1230 + d) if private else None)
+    assert wskp._stream(None).value == (0x1233 if private else 0x1234)
+    assert wskp._stream(Stream()).value == 0x1234 and wskp._stream(77).value == 77

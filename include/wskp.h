@@ -301,12 +301,12 @@ wskp_status_t wskp_mr_blend(wskp_handle_t h, void *stream, int H, int W, const f
  * heads[l] the activated head record of level l, [H>>l, W>>l, 2M]
  * interleaved (as wskp_decode takes it); c [H,W,3] the irradiance; alphas:
  * host array of L-1 device pointers, alphas[l] [H>>l, W>>l] the Eq. 7 blend
- * weight of level l; mod [H,W,3] or NULL; out [H,W,3].  Pools c L-1 times,
- * filters every level, blends from the coarsest and remodulates the finest
+ * weight of level l; mod [H,W,3] or NULL; out [H,W,3].  Filters every level
+ * of the pooled c, blends from the coarsest and remodulates the finest
  * result: the values, bit for bit, of the composition of wskp_pool2,
  * wskp_decode and wskp_mr_blend, in fewer launches.  ws: device workspace of at
- * least wskp_mr_workspace_size bytes (the pooled irradiance of levels
- * 1..L-1, every level's filtered image, the intermediate blends). */
+ * least wskp_mr_workspace_size bytes (every level's filtered image; with
+ * more than three levels also the pooled irradiance of levels 1..L-1). */
 wskp_status_t wskp_mr_workspace_size(wskp_handle_t h, int L, int H, int W, size_t *bytes);
 wskp_status_t wskp_mr_reconstruct(wskp_handle_t h, void *stream, int L, int H, int W,
                                   const float *const *heads, const float *c, const float *const *alphas,

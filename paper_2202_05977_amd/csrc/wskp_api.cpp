@@ -1499,11 +1499,13 @@ extern "C" wskp_status_t wskp_mr_blend(wskp_handle_t h, void *stream, int H, int
     return WSKP_OK;
 }
 
-// Workspace of the multi-resolution reconstruction, float offsets: pooled
-// irradiance cs[l] (l >= 1), filtered images f[l], blends o[l] (1 <= l <= L-2;
-// level 0's blend is the caller's out).
-static wskp_status_t mr_plan(const wskp_ctx *h, int L, int H, int W, size_t *cs, size_t *f, size_t *o,
-                             size_t *total)
+// Levels that the reconstruction filters in one launch, which pools c itself.
+static int mr_joint_levels(int L) { return std::min(L, 3); }
+
+// Workspace of the multi-resolution reconstruction, float offsets: filtered
+// images f[l] and, where there are levels past the joint launch's, the pooled
+// irradiance cs[l] (l >= 1).
+static wskp_status_t mr_plan(const wskp_ctx *h, int L, int H, int W, size_t *cs, size_t *f, size_t *total)
 {
     if (L < 1 || L > WSKP_MAX_LEVELS) return fail(WSKP_E_INVALID_ARG, "L must be in 1..6");
     const int a = 1 << (L - 1);
@@ -1518,9 +1520,8 @@ static wskp_status_t mr_plan(const wskp_ctx *h, int L, int H, int W, size_t *cs,
         return at;
     };
     for (int l = 0; l < L; ++l) {
-        cs[l] = l ? take(l) : 0;
+        cs[l] = l && L > mr_joint_levels(L) ? take(l) : 0;
         f[l] = take(l);
-        o[l] = (l >= 1 && l + 2 <= L) ? take(l) : 0;
     }
     *total = off * sizeof(float);
     return WSKP_OK;
@@ -1529,8 +1530,8 @@ static wskp_status_t mr_plan(const wskp_ctx *h, int L, int H, int W, size_t *cs,
 extern "C" wskp_status_t wskp_mr_workspace_size(wskp_handle_t h, int L, int H, int W, size_t *bytes)
 {
     if (!h || !bytes) return fail(WSKP_E_INVALID_ARG, "NULL argument");
-    size_t cs[WSKP_MAX_LEVELS], f[WSKP_MAX_LEVELS], o[WSKP_MAX_LEVELS];
-    return mr_plan(h, L, H, W, cs, f, o, bytes);
+    size_t cs[WSKP_MAX_LEVELS], f[WSKP_MAX_LEVELS];
+    return mr_plan(h, L, H, W, cs, f, bytes);
 }
 
 extern "C" wskp_status_t wskp_mr_reconstruct(wskp_handle_t h, void *stream, int L, int H, int W,
@@ -1540,8 +1541,8 @@ extern "C" wskp_status_t wskp_mr_reconstruct(wskp_handle_t h, void *stream, int 
 {
     if (!h || !heads || !c || !out || (L > 1 && (!alphas || !ws)))
         return fail(WSKP_E_INVALID_ARG, "NULL argument");
-    size_t cs[WSKP_MAX_LEVELS], f[WSKP_MAX_LEVELS], o[WSKP_MAX_LEVELS], need;
-    wskp_status_t st = mr_plan(h, L, H, W, cs, f, o, &need);
+    size_t cs[WSKP_MAX_LEVELS], f[WSKP_MAX_LEVELS], need;
+    wskp_status_t st = mr_plan(h, L, H, W, cs, f, &need);
     if (st != WSKP_OK) return st;
     for (int l = 0; l < L; ++l)
         if (!heads[l] || (l + 1 < L && !alphas[l])) return fail(WSKP_E_INVALID_ARG, "NULL level pointer");
@@ -1560,7 +1561,7 @@ extern "C" wskp_status_t wskp_mr_reconstruct(wskp_handle_t h, void *stream, int 
     // most 1/64 of the frame, from images pooled by launches of their own
     float *fl[WSKP_MAX_LEVELS];
     for (int l = 0; l < L; ++l) fl[l] = base + f[l];
-    const int joint = std::min(L, 3);
+    const int joint = mr_joint_levels(L);
     const float *cl = c;
     for (int l = 1; l < L && L > joint && e == hipSuccess; ++l) {
         e = launch_pool2(H >> (l - 1), W >> (l - 1), cl, base + cs[l], s);

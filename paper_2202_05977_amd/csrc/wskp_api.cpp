@@ -1156,7 +1156,8 @@ static size_t train_plan(const wskp_ctx *h, int Hm, int Wm, int nf, char *base, 
         o += align_up(floats * sizeof(float));
         return p;
     };
-    size_t mx_in = 10 * (size_t)P, mx_part = tr_wgrad_part_floats(Hm, Wm, 10, ch[0], nf);
+    // mx_in: the pooled input of an encoder (the other convs read theirs in place)
+    size_t mx_in = 0, mx_part = tr_wgrad_part_floats(Hm, Wm, 10, ch[0], nf);
     for (int l = 0; l < L; ++l) {
         const int Hl = Hm >> l, Wl = Wm >> l;
         const long Pl = (long)Hl * Wl;
@@ -1165,11 +1166,9 @@ static size_t train_plan(const wskp_ctx *h, int Hm, int Wm, int nf, char *base, 
             mx_part = std::max(mx_part, tr_wgrad_part_floats(Hl, Wl, ch[l - 1], ch[l], nf));
         }
         if (l + 1 < L) {
-            mx_in = std::max(mx_in, (size_t)(ch[l + 1] + ch[l]) * Pl);
             mx_part = std::max(mx_part, tr_wgrad_part_floats(Hl, Wl, ch[l + 1] + ch[l], ch[l], nf));
         }
     }
-    mx_in = std::max(mx_in, (size_t)ch[0] * P);
     mx_part = std::max(mx_part, tr_wgrad_part_floats(Hm, Wm, ch[0], 2 * M, nf));
     const int ldh = head_grad_stride(M);
     // the input-gradient convs' packed weights (C_out of the forward conv

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from _helpers import to_dev
 from paper_2202_05977_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -39,4 +40,29 @@ def test_multiresolution_workspace(L):
     buf = _guarded(need)
     y = wskp.mr_reconstruct(h, heads, c, alphas, None, ws=buf[:need])
     assert torch.equal(y, wskp.mr_reconstruct(h, heads, c, alphas, None)) and _untouched(buf, need)
+    dn.close()
+
+
+@pytest.mark.parametrize("sizes", [[(64, 64)] * 3, [(40, 72), (64, 32)]])
+def test_training_workspace(sizes):
+    from paper_2202_05977_amd import wskp
+    cfg = synth.HD
+    dn = wskp.Denoiser(cfg, synth.make_weights(cfg, 3), "fp32")
+    frames = []
+    for i, (H, W) in enumerate(sizes):
+        f = to_dev(synth.make_frame(70 + i, H, W))
+        f["out"] = torch.empty_like(f["radiance"])
+        frames.append(f)
+    need = wskp.wskp_train_workspace_size(dn.h, [s[0] for s in sizes], [s[1] for s in sizes])
+    grads = []
+    for buf in (_guarded(need), torch.empty(2 * need, dtype=torch.uint8, device="cuda")):
+        grad = torch.empty(synth.num_weights(cfg), device="cuda")
+        ws = buf[:need] if buf.numel() == need + GUARD else buf
+        wskp.wskp_train_grads(dn.h, frames, [f["clean"] for f in frames], grad, torch.empty(1, device="cuda"), ws)
+        grads.append(grad)
+        assert ws is buf or _untouched(buf, need)
+    assert torch.equal(*grads) and bool(torch.isfinite(grads[0]).all())
+    # 8 crops of 256x256: without room for the decoders' concatenated inputs (201 MB), which
+    # the gradients read in place
+    assert wskp.wskp_train_workspace_size(dn.h, [256] * 8, [256] * 8) < 800 << 20
     dn.close()

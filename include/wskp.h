@@ -60,8 +60,9 @@ typedef enum {
  * always float32. */
 typedef enum {
     WSKP_PREC_FP32 = 0,    /* fp32 operands, fp32 MFMA accumulate; 3x3 convs of frames of at
-                            * least 2^17 pixels take each operand as the exact sum of three
-                            * bf16 parts on the bf16 MFMAs (no less exact, see conv_split.hip) */
+                            * least 2^17 pixels, in nets with enough of their work in layers of
+                            * more than 16 channels, take each operand as the sum of three bf16
+                            * parts on the bf16 MFMAs (no less exact, see conv_split.hip) */
     WSKP_PREC_BF16 = 1,    /* bf16 operands (round to nearest even), fp32 accumulate */
     WSKP_PREC_FP8_E4M3 = 2 /* OCP e4m3 operands with scales, fp32 accumulate */
 } wskp_precision_t;

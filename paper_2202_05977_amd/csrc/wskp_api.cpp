@@ -350,6 +350,25 @@ extern "C" wskp_status_t wskp_repvgg_merge(int cin, int cout, const float *w1, c
     return WSKP_OK;
 }
 
+// Whether a net has the split kernel at all.  It computes 32 output channels at a
+// time: a layer of 16 or fewer fills half of them or less and is slower on it,
+// wider layers are up to 1.8 times as fast, so a net gains by the share of its
+// multiply-adds that lies in wider layers.  Native / split, us, at 368x368 and
+// 720x1280: channels (16), share 0, 33 / 39 and 110 / 135; (16, 32), 0.11, 71 / 79
+// and 266 / 283; (16, 64), 0.15, 91 / 97 and 355 / 363; (16, 256), 0.18, 194 / 200
+// and 918 / 852; (16, 32, 16), 0.33, 95 / 103 and 345 / 337; (16, 32, 64), 0.51,
+// 113 / 114 and 427 / 378; (32, 16), 0.88, 114 / 99 and 463 / 368.
+static bool split_pays(const wskp_ctx *h)
+{
+    double all = 0, wide = 0;
+    for (const LayerPlan &lp : h->layers) {
+        const double macs = std::ldexp((double)lp.Cin * lp.L.Cout, -2 * lp.L.level);
+        all += macs;
+        if (lp.L.Cout > 16) wide += macs;
+    }
+    return 6 * wide >= all;
+}
+
 // The packing of the split kernel's weights from the handle's weight blob.
 static void add_split_jobs(const wskp_ctx *h, PackJobs &jobs)
 {
@@ -528,7 +547,7 @@ extern "C" wskp_status_t wskp_create(const wskp_config_t *cfg, const float *host
                                   : nullptr;
     }
 
-    if (h->prec == WSKP_PREC_FP32 && ks == 3) {
+    if (h->prec == WSKP_PREC_FP32 && ks == 3 && split_pays(h)) {
         h->split = h->layers;
         size_t bytes = 0;
         for (auto &lp : h->split) {

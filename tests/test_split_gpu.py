@@ -99,12 +99,12 @@ def test_split_convs_over_the_whole_range():
     infinity there: the first conv passes depth (0 or 1) on times 3.4e38, the head takes
     2^-125 of it, beside ordinary channels."""
     from paper_2202_05977_amd import wskp
-    cfg = synth.NetConfig(levels=1, channels=(16,), kernel_sizes=(3, 5))
+    cfg = synth.NetConfig(levels=1, channels=(32,), kernel_sizes=(3, 5))
     blob = synth.make_weights(cfg, 4)
-    w0, head = blob[:16 * 90].reshape(16, 10, 3, 3), blob[16 * 90 + 16:-4].reshape(4, 16, 3, 3)
+    w0, head = blob[:32 * 90].reshape(32, 10, 3, 3), blob[32 * 90 + 32:-4].reshape(4, 32, 3, 3)
     w0[0] = 0
     w0[0, 9, 1, 1] = 3.4e38
-    blob[16 * 90] = 0
+    blob[32 * 90] = 0
     head[:, 0] = 0
     head[:, 0, 1, 1] = np.array([1, -1, 1, -1]) * 2.0 ** -125
     fr = synth.make_frame(5, 364, 364)
@@ -145,4 +145,23 @@ def test_nan_gradients_take_no_longer():
     target.fill_(float("nan"))
     t = _time(step)
     assert bool(torch.isnan(grad).any()) and t <= 1.5 * clean
+    dn.close()
+
+
+@pytest.mark.parametrize("channels,split", [((16,), False), ((16, 16, 16), False), ((16, 64), False), ((16, 256), True),
+                                            ((32, 16), True)])
+def test_nets_of_narrow_layers_keep_the_fp32_mfmas(channels, split):
+    """A layer's values do not depend on the frame's tiling, so those of a net that
+    runs one kernel at all sizes are, away from the borders, bitwise those of a
+    small frame cut out of it."""
+    from paper_2202_05977_amd import wskp
+    cfg = synth.NetConfig(levels=len(channels), channels=channels, kernel_sizes=(3, 5))
+    dn = wskp.Denoiser(cfg, synth.make_weights(cfg, 4), "fp32")
+    fr = synth.make_frame(5, 364, 364)
+    dn(to_dev(fr))
+    a = dn.intermediate([364], [364], 0, 200)[100:228, 120:248].clone()
+    dn(to_dev({k: np.ascontiguousarray(v[100:228, 120:248]) for k, v in fr.items()}))
+    b = dn.intermediate([128], [128], 0, 200)
+    same = torch.equal(a[24:-24, 24:-24], b[24:-24, 24:-24])
+    assert same == (not split)
     dn.close()

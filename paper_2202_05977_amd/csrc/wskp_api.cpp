@@ -152,13 +152,20 @@ static void *g_scratch_ptr[kMaxDevices];
 
 // FP32 3x3 convs: frames of at least this many pixels run the split kernel, in
 // denoising and in training alike (a frame's result depends neither on its
-// batch nor on who asks): 720p, four levels, 985 us against 1460.  Smaller frames
-// keep v_mfma_f32_16x16x4f32.  The smallest are faster with it (128 x 128, three
-// levels: 47 us on cut tiles against 68), and training needs it, whose crops
-// are of 256 x 256 and less: a gradient is taken through the forward pass's ReLU
-// masks, and any change of the forward rounding carries a few pre-activations
-// within it of zero to the other side, which moves the gradient of a batch of
-// such crops by 2e-6 to 6e-5 of its norm.  720p is 7 times above the line.
+// batch nor on who asks), smaller ones v_mfma_f32_16x16x4f32 on cut tiles.  Native /
+// split, us a frame:
+//                          128x128   192x192   256x256   360x360   512x512
+//   3 levels, 16..64       43 / 57   54 / 62   61 / 66  109 / 111  145 / 133
+//   4 levels, 32..128      98 / 139 148 / 152 175 / 159 341 / 241  432 / 308
+// The line is where the narrow net's kernels cross.  The wide net's cross at
+// about 200x200: its frames from there to the line take up to 1.4 times as
+// long as the split kernel would.
+// Gradients move by more than the sums' rounding where a pre-activation within it of
+// zero falls to the other side, on either kernel: relative L2 error against
+// float64, 4 levels, 8 seeds, median (largest): 256x256 1.1e-5 (8.3e-5) native,
+// 1.8e-7 (8.2e-5) split; 384x384 1.2e-5 (4.2e-5), 1.4e-5 (9.8e-5); 512x512 1.4e-5
+// (2.7e-4), 6.1e-6 (2.6e-3).  Training crops below the line keep the native
+// kernel's.
 static constexpr long kSplitPixels = 1L << 17;
 
 static constexpr int kRingSlots = 8;

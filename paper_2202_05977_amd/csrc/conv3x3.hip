@@ -906,6 +906,16 @@ int conv_fp32_tiles(ConvLayer &L, int n, const int *H, const int *W)
     return blocks;
 }
 
+// fp8: 4-row tiles where 8-row ones are no more than the CUs, each of which would
+// have a single workgroup and its serial chain of chunks.  The 4-level net, us with 8
+// rows / 4 rows / this rule: 64x96 99 / 80 / 80, 256x256 111 / 92 / 90, 360x640 141 /
+// 126 / 127, 720x1280 275 / 310 / 272, 1080x1920 554 / 633 / 554.  Every output's
+// order of summation is the same.
+int conv_fp8_rows(const ConvLayer &L, int mode, int n, const int *H, const int *W)
+{
+    return mode != CONV_PACK && conv_grid(L, n, H, W) <= 256 ? 4 : L.th;
+}
+
 // The cut tiles of conv_fp32_tiles: TH rows, one block.
 template <int MODE, int EPI, int TH, int CK>
 static bool launch_fp32_small(const ConvLayer &L, const FrameArg &fa, int blocks, hipStream_t s)
@@ -963,6 +973,13 @@ static void launch_one(const ConvLayer &L, const FrameArg &fa, int blocks, hipSt
             hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, kTHD, NB, OutT>), dim3(blocks),
                                dim3(kThreads), 0, s, L, fa);
         return;
+    }
+    if constexpr (PREC == 2 && MODE != CONV_PACK) {
+        if (L.th == 4) {
+            hipLaunchKernelGGL((conv3x3_kernel<2, MODE, EPI, 4, CK, NB, SrcT, OutT>), dim3(blocks), dim3(kThreads), 0, s,
+                               L, fa);
+            return;
+        }
     }
     // fp32 activations travel with the fp32 MFMA form; the bf16 and fp8 forms
     // keep bf16 activations in memory

@@ -775,6 +775,7 @@ static std::vector<ConvGroup> plan_convs(const wskp_ctx *h, int n, const int *Hs
         for (const LayerPlan &lp : split ? h->split : h->layers) {
             ConvLaunch c{lp.L, lp.mode, lp.epi, split, 0};
             if (runs_conv_bf16(h->prec, lp)) c.L.th = conv_bf16_rows(c.L, g.n, Hs + f, Ws + f);
+            if (h->prec == WSKP_PREC_FP8_E4M3) c.L.th = conv_fp8_rows(c.L, lp.mode, g.n, Hs + f, Ws + f);
             c.blocks = conv_grid(c.L, g.n, Hs + f, Ws + f);
             if (h->prec == WSKP_PREC_FP32 && !split) c.blocks = conv_fp32_tiles(c.L, g.n, Hs + f, Ws + f);
             // 4-row tiles where 8-row ones leave CUs without their two workgroups

@@ -256,6 +256,8 @@ hipError_t launch_conv(const ConvLayer &L, int mode, int epi, int prec, const Fr
 int conv_grid(const ConvLayer &L, int n, const int *H, const int *W);
 // fp32 native convs: sets the layer's tiling for these sizes, returns its grid
 int conv_fp32_tiles(ConvLayer &L, int n, const int *H, const int *W);
+// fp8 convs: tile rows for these sizes
+int conv_fp8_rows(const ConvLayer &L, int mode, int n, const int *H, const int *W);
 // FP32 3x3 convs on the bf16 matrix cores (conv_split.hip): sets the layer's
 // tiling for Cin input channels (Cout set), sizes its packed weights, launches
 // it.

@@ -1526,7 +1526,7 @@ extern "C" wskp_status_t wskp_mr_blend(wskp_handle_t h, void *stream, int H, int
 }
 
 // Levels that the reconstruction filters in one launch, which pools c itself.
-static int mr_joint_levels(int L) { return std::min(L, 3); }
+static int mr_joint_levels(int L) { return std::min(L, kMrJoint); }
 
 // Workspace of the multi-resolution reconstruction, float offsets: filtered
 // images f[l] and, where there are levels past the joint launch's, the pooled

@@ -296,8 +296,9 @@ int decode_grid(const DecodeCfg &dc, int n, const int *H, const int *W);
 DecodeCfg decode_frames_cfg(const DecodeCfg &dc, int n, const int *H, const int *W);
 hipError_t launch_decode_tensors(const DecodeCfg &dc, int N, int H, int W, const float *head,
                                  const float *c, const float *mod, float *out, hipStream_t s);
-// wskp_decode of 1..3 levels of one frame in one launch, level l's irradiance
+// wskp_decode of 1..kMrJoint levels of one frame in one launch, level l's irradiance
 // the l times pooled c, no remodulation
+constexpr int kMrJoint = 3;
 hipError_t launch_decode_levels(const DecodeCfg &dc, int levels, int H, int W, const float *const *heads,
                                 const float *c, float *const *outs, hipStream_t s);
 // act_ld > 0 (training): grad_head receives the gradient of the head conv's

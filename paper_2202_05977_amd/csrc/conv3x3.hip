@@ -570,7 +570,9 @@ __global__ __launch_bounds__(kThreads, (MODE == CONV_PACK && PREC == 1 && KS == 
 }
 
 // =============================================================================
-// bf16 decoder and head convs with direct-to-LDS buffer loads
+// bf16 convs of an odd number of output blocks (48, 80 channels, the head) with
+// direct-to-LDS buffer loads, one 16-channel block per workgroup; layers of pairs
+// of blocks run conv_bf16.hip
 // =============================================================================
 // Every 16-byte slot of the input halo (8 bf16 channels of one pixel) and of
 // the weight slice goes from memory straight into LDS with
@@ -600,26 +602,25 @@ __device__ __forceinline__ void load_lds16(rsrc_t r, unsigned char *lds, unsigne
 constexpr unsigned kOutOfRange = 0x7ffffff0u;
 
 // Each wave computes HW = TH/4 output rows of the tile (both 16-pixel column
-// blocks, all NB output blocks).  For one column offset dx it reads the A
+// blocks).  For one column offset dx it reads the A
 // fragments of its HW+KS-1 input rows once and uses each for up to KS
 // vertical taps dy (input row r+dy feeds output row r), so a 3x3 chunk costs
 // 6 (HW+2) A fragment reads instead of 18 HW: the LDS bytes per MFMA, which
 // bound this loop, fall with HW.
 // Workgroups per CU that the stage's LDS (160 KiB per CU) admits, at most
-// four (at TH = 8: 40, 49 and 58 KiB for 2, 3 and 4 output blocks, so 4, 3
-// and 2; 5x5 layers with one output block, 52 KiB, 3); the register budget
+// four (at TH = 8: 3x3, 31 KiB, four; 5x5, 52 KiB, three); the register budget
 // is capped to match.
-constexpr int direct_stage_bytes(int NB, int KS, int TH)
+constexpr int direct_stage_bytes(int KS, int TH)
 {
-    return ((TH + KS - 1) * (kConvTW + KS - 1) * 64 + NB * 16 * KS * KS * 64 + 1023) / 1024 * 1024;
+    return ((TH + KS - 1) * (kConvTW + KS - 1) * 64 + 16 * KS * KS * 64 + 1023) / 1024 * 1024;
 }
-constexpr int direct_min_wg(int NB, int KS, int TH)
+constexpr int direct_min_wg(int KS, int TH)
 {
-    return 163840 / direct_stage_bytes(NB, KS, TH) < 4 ? 163840 / direct_stage_bytes(NB, KS, TH) : 4;
+    return 163840 / direct_stage_bytes(KS, TH) < 4 ? 163840 / direct_stage_bytes(KS, TH) : 4;
 }
 
-template <int MODE, int EPI, int TH, int NB, typename OutT, int KS = 3>
-__global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_bf16_direct(ConvLayer L, FrameArg fa)
+template <int MODE, int EPI, int TH, typename OutT, int KS = 3>
+__global__ __launch_bounds__(kThreads, direct_min_wg(KS, TH)) void conv3x3_bf16_direct(ConvLayer L, FrameArg fa)
 {
     constexpr int CK = 32, WP = kConvTW + KS - 1, HP = TH + KS - 1, NPIX = HP * WP;
     constexpr int A_SLOTS = NPIX * 4;
@@ -631,7 +632,7 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
     // on distinct banks (a 592-byte padded row costs 4 extra LDS cycles per
     // read on gfx950).
     constexpr int BSK = NK * 32;
-    constexpr int B_SLOTS = NB * 16 * BSK / 8;
+    constexpr int B_SLOTS = 16 * BSK / 8;
     // The stage is one array of 16-byte slots, halo first, weights right
     // after it; load instruction j fills slots [64j, 64j + 64).  The
     // instruction that straddles the boundary is issued twice, once per
@@ -640,8 +641,8 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
     constexpr int INS = (SLOTS + 63) / 64;
     constexpr int PW = (INS + 3) / 4;                      // load instructions per wave
     constexpr int A_BYTES = A_SLOTS * 16, STAGE = INS * 1024;
-    static_assert(STAGE == direct_stage_bytes(NB, KS, TH), "stage size");
-    constexpr int MB = TH / 2, NC = NB * 16, HW = TH / 4;
+    static_assert(STAGE == direct_stage_bytes(KS, TH), "stage size");
+    constexpr int MB = TH / 2, HW = TH / 4;
     static_assert(TH % 4 == 0, "each wave owns TH/4 whole rows");
     __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGE];
 
@@ -700,7 +701,7 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
         const int c0 = cc * CK;
         const bool up = MODE != CONV_CAT || c0 < L.C0;
         const unsigned da = (unsigned)((up ? c0 : c0 - L.C0) * 2);
-        const unsigned wb = (unsigned)((cc * L.Cout_pad + g * NC) * BSK * 2);
+        const unsigned wb = (unsigned)((cc * L.Cout_pad + g * 16) * BSK * 2);
 #pragma unroll
         for (int k = 0; k < PW; ++k) {
             const int ins = wave + 4 * k;
@@ -716,11 +717,9 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
         }
     };
 
-    f32x4 acc[MB][NB];
+    f32x4 acc[MB][1];
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[i][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < MB; ++i) acc[i][0] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // MFMAs of one chunk from the stage at As (halo) / As + A_BYTES (weights)
     auto compute = [&](const unsigned char *As) {
@@ -739,19 +738,14 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
 #pragma unroll
             for (int dy = 0; dy < KS; ++dy) {
                 const int s = dy * KS + dx;
-                bf16x8 b[NB];
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    b[nb] = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u16x8 *>(Bs + ((nb * 16 + lw) * BSK + s * 32 + bq * 8) * 2));
+                const bf16x8 b = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const u16x8 *>(Bs + (lw * BSK + s * 32 + bq * 8) * 2));
 #pragma unroll
                 for (int r = 0; r < HW; ++r)
 #pragma unroll
                     for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
-                            acc[2 * r + cb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                b[nb], a[r + dy][cb], acc[2 * r + cb][nb], 0, 0, 0);
+                        acc[2 * r + cb][0] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a[r + dy][cb], acc[2 * r + cb][0], 0, 0, 0);
             }
         }
     };
@@ -765,9 +759,9 @@ __global__ __launch_bounds__(kThreads, direct_min_wg(NB, KS, TH)) void conv3x3_b
         lds_barrier();   // the stage has been read before it is refilled
         if (cc + 1 < nchunks) issue(cc + 1, smem);
     }
-    EpiConsts<1, NB, kHead<EPI>> ec;
+    EpiConsts<1, 1, kHead<EPI>> ec;
     ec.load(L, g);
-    conv_epilogue<1, EPI, TH, NB, OutT>(L, fd, g, x0, y0, Hl, Wl, acc, ec);
+    conv_epilogue<1, EPI, TH, 1, OutT>(L, fd, g, x0, y0, Hl, Wl, acc, ec);
 }
 
 // =============================================================================
@@ -808,12 +802,13 @@ static bool uses_direct(int prec, int mode, int CK, int ks)
 bool conv_uses_direct(int prec, int mode, int CK, int ks) { return uses_direct(prec, mode, CK, ks); }
 
 // Tile rows per layer: the input layer uses kTHP; the direct-load kernel uses
-// kTHD, or 4 rows (and one output block per workgroup) on the levels from
-// WSKP_COARSE_LEVEL on, which have few pixels, so that they still spread
-// over all CUs, unless the layer passes on 2x2 means (that needs whole row
-// pairs per wave, 8 rows).  From level 4: with level 3 on 4-row tiles too
-// (the fourth level of the 720p net, 160 x 90) one frame's launch was
-// slightly faster alone but three-stream throughput 1 % lower.
+// kTHD, or 4 rows on the levels from WSKP_COARSE_LEVEL on, which have few
+// pixels, so that they still spread over all CUs, unless the layer passes on
+// 2x2 means (that needs whole row pairs per wave, 8 rows).  From level 4: with
+// level 3 on 4-row tiles too (the fourth level of the 720p net, 160 x 90) one
+// frame's launch was slightly faster alone but three-stream throughput 1 %
+// lower.  (Layers of conv_bf16.hip choose theirs for each launch, and so do
+// fp32 and fp8 layers.)
 #ifndef WSKP_COARSE_LEVEL
 #define WSKP_COARSE_LEVEL 4
 #endif
@@ -950,10 +945,10 @@ static void launch_one(const ConvLayer &L, const FrameArg &fa, int blocks, hipSt
     if constexpr (WSKP_CONV_DIRECT && NB == 1 && PREC == 1 && CK == 32 && (MODE == CONV_CAT || MODE == CONV_PLAIN)) {
         if (L.ks == 5) {
             if (L.th == 4)
-                hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, 4, 1, OutT, 5>), dim3(blocks), dim3(kThreads), 0, s,
+                hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, 4, OutT, 5>), dim3(blocks), dim3(kThreads), 0, s,
                                    L, fa);
             else
-                hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, kTHD, 1, OutT, 5>), dim3(blocks), dim3(kThreads),
+                hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, kTHD, OutT, 5>), dim3(blocks), dim3(kThreads),
                                    0, s, L, fa);
             return;
         }
@@ -965,12 +960,12 @@ static void launch_one(const ConvLayer &L, const FrameArg &fa, int blocks, hipSt
             return;
         }
     }
-    if constexpr (WSKP_CONV_DIRECT && PREC == 1 && CK == 32 && (MODE == CONV_CAT || MODE == CONV_PLAIN)) {
+    if constexpr (WSKP_CONV_DIRECT && NB == 1 && PREC == 1 && CK == 32 && (MODE == CONV_CAT || MODE == CONV_PLAIN)) {
         if (L.th == 4)
-            hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, 4, NB, OutT>), dim3(blocks),
+            hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, 4, OutT>), dim3(blocks),
                                dim3(kThreads), 0, s, L, fa);
         else
-            hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, kTHD, NB, OutT>), dim3(blocks),
+            hipLaunchKernelGGL((conv3x3_bf16_direct<MODE, EPI, kTHD, OutT>), dim3(blocks),
                                dim3(kThreads), 0, s, L, fa);
         return;
     }

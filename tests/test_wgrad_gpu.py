@@ -109,3 +109,63 @@ def test_infinite_input_in_a_corner(y, x):
     assert np.array_equal(np.isnan(g), np.isnan(ref)) and np.isnan(ref).sum() == 16 * 4
     fin = np.isfinite(ref)
     assert fin.sum() == 16 * 86 and rel_l2(g[fin], ref[fin]) <= TOL_GRAD
+
+
+TWO = synth.NetConfig(levels=2, channels=(16, 32), kernel_sizes=(3, 5))
+
+
+@pytest.mark.parametrize("cfg,sizes", [
+    # 1040 32-row strips at level 0, 1040 16-row strips at level 1, each ending 4 and 2 rows into its
+    # last; the input gradients of every kind on 8-row tiles (2064 of them at level 1)
+    (TWO, [(2052, 4)] * 16),
+    # 32-row strips of several columns, the last half a strip wide
+    (TWO, [(180, 176)] * 16),
+    # a forward pass on the split kernel
+    (synth.SMALL, [(364, 364)]),
+])
+def test_large_batches_against_oracle(cfg, sizes):
+    from paper_2202_05977_amd import wskp
+    blob = synth.make_weights(cfg, 8)
+    host = [synth.make_frame(80 + i % 2, H, W) for i, (H, W) in enumerate(sizes)]
+    frames = []
+    for fr in host:
+        f = to_dev(fr)
+        f["out"] = torch.empty_like(f["radiance"])
+        frames.append(f)
+    dn = wskp.Denoiser(cfg, blob, "fp32")
+    grad, loss = torch.empty(blob.size, device="cuda"), torch.empty(1, device="cuda")
+    ws = torch.empty(wskp.wskp_train_workspace_size(dn.h, [s[0] for s in sizes], [s[1] for s in sizes]),
+                     dtype=torch.uint8, device="cuda")
+    wskp.wskp_train_grads(dn.h, frames, [f["clean"] for f in frames], grad, loss, ws)
+    g = grad.cpu().numpy().astype(np.float64)
+    # (two distinct frames, so many times each)
+    two = [oracle.train_grads(fr, fr["clean"], blob, cfg) for fr in host[:2]]
+    ref = sum(t[1] for t in two) / len(two)
+    assert abs(float(loss) - sum(t[0] for t in two) / len(two)) <= 1e-5 * float(loss)
+    off = 0
+    for name, ci, co in synth.conv_shapes(cfg):
+        n = ci * co * 9 + co
+        assert rel_l2(g[off:off + n], ref[off:off + n]) <= TOL_GRAD, name
+        off += n
+    dn.close()
+
+
+def test_split_weights_follow_an_adam_step():
+    """A frame of the split kernel after a step equals, bit for bit, that of a new handle
+    with the weights read back."""
+    from paper_2202_05977_amd import wskp
+    cfg = synth.SMALL
+    blob = synth.make_weights(cfg, 8)
+    dn = wskp.Denoiser(cfg, blob, "fp32")
+    f = to_dev(synth.make_frame(9, 364, 364))
+    before = dn(f).clone()
+    n = blob.size
+    g = torch.randn(n, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    wskp.wskp_adam(dn.h, g, torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda"), 1, lr=1e-3)
+    w = torch.empty(n, device="cuda")
+    wskp.wskp_get_weights(dn.h, w)
+    new = wskp.Denoiser(cfg, w.cpu().numpy(), "fp32")
+    after = dn(f)
+    assert torch.equal(after, new(f)) and not torch.equal(after, before)
+    dn.close()
+    new.close()

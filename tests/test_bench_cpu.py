@@ -34,3 +34,12 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=120)
     assert p.returncode != 0
     assert "one GPU" in p.stdout + p.stderr
+
+
+def test_fp32_peak_is_that_of_the_instructions_that_run():
+    """720p fp32 convs run as six bf16 products each; small frames and 5x5 convs on the
+    fp32 MFMAs."""
+    assert bench.mfma_peak("fp32", synth.HD, 720, 1280) == 2.5e15 / 6
+    assert bench.mfma_peak("fp32", synth.HD, 256, 256) == bench.PEAK["fp32"]
+    assert bench.mfma_peak("fp32", synth.REPVGG, 720, 1280) == bench.PEAK["fp32"]
+    assert bench.mfma_peak("bf16", synth.HD, 720, 1280) == 2.5e15

@@ -24,7 +24,7 @@
 //   dgrad  gin[p][ci] = sum_{tap,co} gm[p - off(tap)][co] w[co][ci][tap]:
 //          itself a 3x3 conv of gm with the kernel flipped and its channel
 //          axes swapped, run by the split conv kernel (conv_split.hip) on
-//          weights that conv_split_pack lays out for it; the head's 2M
+//          weights that conv_pack_kernel lays out for it; the head's 2M
 //          output channels are padded with zeros to a multiple of 16 (its
 //          gradient dh is written with that row stride)
 //   wgrad  dw[co][ci][tap] = sum_p gm[p][co] in[p + off(tap)][ci],

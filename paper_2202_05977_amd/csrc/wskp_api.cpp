@@ -1330,7 +1330,10 @@ extern "C" wskp_status_t wskp_train_grads(wskp_handle_t h, void *stream, int n, 
         // 4-row tiles below two workgroups per CU, as in plan_convs; through the
         // 2x2 mean below eight: that epilogue reads and writes four pixels for
         // each of the conv's, and a single round of tall tiles leaves the memory idle
-        // meanwhile (8 crops, 64 -> 32 channels at 128x128: 111 us, 98 so)
+        // meanwhile.  A step's gradients, us with a line of 512 / 2048 there, 4-level
+        // net: 1 crop of 256x256 596 / 594, 4 1290 / 1288, 8 2224 / 2204, 16 4148 /
+        // 4097, 8 of 312x200 2517 / 2493, 2 of 512x512 1975 / 1951, 8 of 128x128 819 /
+        // 818, 32 of 64x64 924 / 927
         if (blocks < (epi == EPI_BWD_POOL ? 2048 : 512) && epi != EPI_BWD_CAT) {
             c.th = 4;
             blocks = conv_grid(c, nf, hv.data(), wv.data());

@@ -901,14 +901,17 @@ int conv_fp32_tiles(ConvLayer &L, int n, const int *H, const int *W)
     return blocks;
 }
 
-// fp8: 4-row tiles where 8-row ones are no more than the CUs, each of which would
-// have a single workgroup and its serial chain of chunks.  The 4-level net, us with 8
-// rows / 4 rows / this rule: 64x96 99 / 80 / 80, 256x256 111 / 92 / 90, 360x640 141 /
-// 126 / 127, 720x1280 275 / 310 / 272, 1080x1920 554 / 633 / 554.  Every output's
-// order of summation is the same.
+// fp8: 4-row tiles where 8-row ones leave most CUs with a single workgroup and its
+// serial chain of chunks: up to one for each CU, or up to 1.5 where a workgroup has
+// one or two output blocks (4 rows / 8 rows, us: the 4-level net at 208x384, 312
+// tiles at full resolution, 98 / 100; 64 and 128 channels at 272x480, 272 tiles of
+// four blocks at half resolution, 79 / 76).  The 4-level net with 8 rows / 4 rows / this
+// rule: 64x96 99 / 80 / 80, 256x256 111 / 92 / 90, 360x640 141 / 126 / 127,
+// 720x1280 275 / 310 / 272, 1080x1920 554 / 633 / 554.  Every output's order of
+// summation is the same.
 int conv_fp8_rows(const ConvLayer &L, int mode, int n, const int *H, const int *W)
 {
-    return mode != CONV_PACK && conv_grid(L, n, H, W) <= 256 ? 4 : L.th;
+    return mode != CONV_PACK && conv_grid(L, n, H, W) <= (L.NB > 2 ? 256 : 384) ? 4 : L.th;
 }
 
 // The cut tiles of conv_fp32_tiles: TH rows, one block.

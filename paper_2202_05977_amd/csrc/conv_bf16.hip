@@ -26,9 +26,11 @@
 // epilogue (59), 16-row tiles (60).
 //
 // Measured against 16x16x32 MFMAs with per-chunk address arithmetic and
-// 32-byte stores, frame times, bitwise the same output: 3x3 net at 720p 242 ->
-// 232 us, batch of 360p..1440p 1573 -> 1538; 5x5 net at 720p 463 -> 431; the
-// six-kernel net at 664x376 119 -> 107.
+// 32-byte stores, both in turn on one card, frame times, bitwise the same output:
+// 5x5 net at 720p 474 -> 451 us, the six-kernel net at 664x376 123 -> 114; the 3x3
+// net at 720p 250 -> 249 and a batch of 360p..1440p 1600 -> 1584, hardly more than
+// the runs differ: there the card's power, not the kernel's issue, sets the
+// decoders' pace (a card that holds its clock: 243 -> 234).
 //
 // LDS images.  Halo: 64 bytes a pixel, its four 16-byte channel groups at
 // position g ^ ((column >> 1) & 3), so that the 8 consecutive pixels that one

@@ -25,8 +25,8 @@
 // wave reads the fragments of its HW + 2 input rows once for up to three
 // vertical taps: 75 bytes of LDS per clock and CU against the 128 it has.
 //
-// Measured, 1280x720 hd net: frame 1461 -> 988 us; dec0 (96 -> 32 channels)
-// 456 -> 251 us = 203 TFLOP/s of fp32 work, 1218 of bf16 MFMAs; the card runs
+// Measured, 1280x720 hd net: frame 1458 -> 945 us; dec0 (96 -> 32 channels)
+// 456 -> 245 us = 208 TFLOP/s of fp32 work, 1248 of bf16 MFMAs; the card runs
 // 32x32x16 MFMAs on random data from registers at 1830 (1.83 GHz: the clock
 // gives way).
 //

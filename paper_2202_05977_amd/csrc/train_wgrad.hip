@@ -23,11 +23,11 @@
 // Each strip's sums go to `part` and `partb`, which the reduce kernels of
 // train.hip add in a fixed order.
 //
-// Measured, 8 crops of 256x256: 96 -> 32 channels 373 -> 181 us (160 TFLOP/s of
-// fp32 work, 960 of bf16 MFMAs), 160 -> 64 304 -> 160, all eight layers 1190 ->
-// 670 us per step.  What bounds it now: MFMA issue (16x16x32 takes 19.5 cycles of
+// Measured, 8 crops of 256x256: 96 -> 32 channels 373 -> 166 us (175 TFLOP/s of
+// fp32 work, 1050 of bf16 MFMAs), 160 -> 64 304 -> 145, all eight layers 1187 ->
+// 620 us per step.  What bounds it now: MFMA issue (16x16x32 takes 19.5 cycles of
 // 16 from two waves per SIMD) and staging, which each of the two layers with
-// 10 channels on a side (61 us) is bound by alone.
+// 10 channels on a side (57 us) is bound by alone.
 #include "conv_device.h"
 
 namespace wskp {

@@ -23,6 +23,8 @@
 // box sums of those terms).
 #include "wskp_internal.h"
 
+#include <type_traits>
+
 namespace wskp {
 
 // 32 x 16-centre tiles (8 row groups of kDTY/8 rows).  The adjoint's
@@ -35,9 +37,9 @@ static_assert(kDTY % 8 == 0, "8 row groups of kDTY/8 rows");
 #define WSKP_DECODE_MIN_WG 4
 #endif
 
-// Equal-size frames as plain tensors.  MR (the multi-resolution
-// reconstruction): one frame at `levels` resolutions, level l's head record and
-// output at head_l[l] and out_l[l], the irradiance c at full resolution.
+// Equal-size frames as plain tensors.  (What only the multi-resolution form needs is
+// in a structure of its own: each launch of these kernels fetches its arguments
+// cold, and 100 bytes more cost each 0.2 us.)
 struct DecodeTensors {
     int N, H, W;
     const float *head, *c, *mod;   // mod may be null
@@ -47,8 +49,11 @@ struct DecodeTensors {
     float *grad_head;   // [N,H,W,2M]
     float4 *scratch;    // [N,M,H,W] x (u_0, u_1, u_2, dS)
     float *dlogit;      // [N,M,H,W]: the logits' gradients, pass A to pass B
-    // MR only (no longer than needed: every launch of these kernels fetches its
-    // arguments cold, and 96 bytes more cost each 0.2 us)
+};
+// MR (the multi-resolution reconstruction): one frame at `levels` resolutions, level
+// l's head record and output at head_l[l] and out_l[l], the irradiance c at full
+// resolution.
+struct DecodeLevels : DecodeTensors {
     int levels;
     const float *head_l[kMrJoint];
     float *out_l[kMrJoint];
@@ -73,9 +78,10 @@ __device__ __host__ __forceinline__ int decode_tiles(int H, int W)
 }
 
 // This workgroup's tile; false past the last.
-template <bool MR>
-__device__ __forceinline__ bool decode_locate(const DecodeCfg &dc, const DecodeTensors &dt, DecodeIO &io)
+template <typename Tensors>
+__device__ __forceinline__ bool decode_locate(const DecodeCfg &dc, const Tensors &dt, DecodeIO &io)
 {
+    constexpr bool MR = std::is_same<Tensors, DecodeLevels>::value;
     int t, f = 0;
     io = DecodeIO{};
     io.H = dt.H;
@@ -149,6 +155,8 @@ __device__ __forceinline__ void pooled_c(const float *c, int W0, int y, int x, f
 }
 
 enum DecodeKind { DK_TENSORS = 1, DK_ADJ_A = 2, DK_MR = 3 };
+template <int KIND>
+using DecodeArgs = typename std::conditional<KIND == DK_MR, DecodeLevels, DecodeTensors>::type;
 
 // e^x for the softmax numerators (x = l_i - max_j l_j <= 0): the hardware
 // 2^x of x log2(e) instead of the library expf.  Relative error about
@@ -322,12 +330,12 @@ constexpr unsigned kNoPixel = 0xfffffff0u;
 // instead of 33.5 in five (two pools, three decodes).
 template <int M, int KIND, int RM>
 __global__ __launch_bounds__(kThreads, M <= 5 ? WSKP_DECODE_MIN_WG : (KIND == DK_ADJ_A ? 2 : 3)) void
-decode_fwd_kernel(DecodeCfg dc, DecodeTensors dt)
+decode_fwd_kernel(DecodeCfg dc, DecodeArgs<KIND> dt)
 {
     constexpr bool ADJ = KIND == DK_ADJ_A, MR = KIND == DK_MR;
     extern __shared__ float4 lds4[];
     DecodeIO io;
-    if (!decode_locate<MR>(dc, dt, io)) return;
+    if (!decode_locate(dc, dt, io)) return;
     const int x0 = io.x0, y0 = io.y0;
 
     const int R = dc.R;
@@ -823,14 +831,15 @@ __global__ __launch_bounds__(kFThreads, 4) void decode_tile_kernel(DecodeCfg dc,
 // ACT (training): dW_i is taken on through softplus' (the logistic of h, = 1 -
 // e^{-W} = -expm1(-W) in terms of W = softplus(h), accurate also where W is
 // tiny), and the record, the gradient of the head conv's output, is written
-// with rows of act_ld floats, zeros beyond 2M; grad_c is not.
+// with rows of kActLd floats, zeros beyond 2M; grad_c is not.
+constexpr int kActLd = 16;   // 2M padded to a multiple of 16, M <= 8
 template <int M, int RM, bool ACT>
 __global__ __launch_bounds__(kThreads) void decode_adj_b_kernel(DecodeCfg dc, DecodeTensors dt,
-                                                                 float *grad_c, int act_ld)
+                                                                 float *grad_c)
 {
     extern __shared__ float4 lds4[];
     DecodeIO io;
-    if (!decode_locate<false>(dc, dt, io)) return;
+    if (!decode_locate(dc, dt, io)) return;
     const int x0 = io.x0, y0 = io.y0;
     const int R = dc.R;
     const int HX = halo_stride(R), HXY = HX * (kDTY + 2 * R);
@@ -893,15 +902,15 @@ __global__ __launch_bounds__(kThreads) void decode_adj_b_kernel(DecodeCfg dc, De
         if (y < H && x < W) {
             const size_t pix = (size_t)y * W + x;
             if constexpr (ACT) {
-                float *dh = dt.grad_head + ((size_t)fidx * P + pix) * act_ld;
-                float rec[16];   // act_ld is 16: 2M padded to a multiple of 16, M <= 8
+                float *dh = dt.grad_head + ((size_t)fidx * P + pix) * kActLd;
+                float rec[kActLd];
 #pragma unroll
-                for (int j = 0; j < 16; ++j) {
+                for (int j = 0; j < kActLd; ++j) {
                     rec[j] = 0.f;
                     if (j < M) rec[j] = dwv[o][j < M ? j : 0] * -expm1f(-wvv[o][j < M ? j : 0]);
                     else if (j < 2 * M) rec[j] = gload(io.dlogit + (size_t)(j - M) * P + pix);
                 }
-                store_floats<16>(dh, rec);
+                store_floats<kActLd>(dh, rec);
             } else {
                 float rec[2 * M];
 #pragma unroll
@@ -937,7 +946,7 @@ static void allow_lds(K kernel, size_t bytes)
 }
 
 template <int KIND>
-static hipError_t launch_decode(const DecodeCfg &dc, const DecodeTensors &dt, int blocks, hipStream_t s)
+static hipError_t launch_decode(const DecodeCfg &dc, const DecodeArgs<KIND> &dt, int blocks, hipStream_t s)
 {
     if (blocks <= 0) return hipSuccess;
     const size_t lds = decode_lds_bytes(dc);
@@ -1053,7 +1062,7 @@ hipError_t launch_decode_levels(const DecodeCfg &dc, int levels, int H, int W, c
                                 const float *c, float *const *outs, hipStream_t s)
 {
     if (levels < 1 || levels > kMrJoint) return hipErrorInvalidValue;
-    DecodeTensors dt{};
+    DecodeLevels dt{};
     dt.N = 1;
     dt.H = H;
     dt.W = W;
@@ -1075,16 +1084,15 @@ size_t decode_backward_scratch_bytes(const DecodeCfg &dc, int N, int H, int W)
 }
 
 template <int M, bool ACT>
-static hipError_t launch_adj_b(const DecodeCfg &dc, const DecodeTensors &dt, int blocks, float *grad_c, int act_ld,
-                               hipStream_t s)
+static hipError_t launch_adj_b(const DecodeCfg &dc, const DecodeTensors &dt, int blocks, float *grad_c, hipStream_t s)
 {
     const size_t lds = adj_b_lds_bytes(dc);
     if (dc.R <= 5) {
         allow_lds(decode_adj_b_kernel<M, 5, ACT>, lds);
-        hipLaunchKernelGGL((decode_adj_b_kernel<M, 5, ACT>), dim3(blocks), dim3(kThreads), lds, s, dc, dt, grad_c, act_ld);
+        hipLaunchKernelGGL((decode_adj_b_kernel<M, 5, ACT>), dim3(blocks), dim3(kThreads), lds, s, dc, dt, grad_c);
     } else {
         allow_lds(decode_adj_b_kernel<M, 7, ACT>, lds);
-        hipLaunchKernelGGL((decode_adj_b_kernel<M, 7, ACT>), dim3(blocks), dim3(kThreads), lds, s, dc, dt, grad_c, act_ld);
+        hipLaunchKernelGGL((decode_adj_b_kernel<M, 7, ACT>), dim3(blocks), dim3(kThreads), lds, s, dc, dt, grad_c);
     }
     return hipGetLastError();
 }
@@ -1107,12 +1115,12 @@ hipError_t launch_decode_backward(const DecodeCfg &dc, int N, int H, int W, cons
     const int blocks = N * decode_tiles(H, W);
     hipError_t e = launch_decode<DK_ADJ_A>(dc, dt, blocks, s);
     if (e != hipSuccess) return e;
-    if (act_ld != 0 && act_ld != 16) return hipErrorInvalidValue;
+    if (act_ld != 0 && act_ld != kActLd) return hipErrorInvalidValue;
     switch (dc.M) {
 #define WSKP_M(m)                                                                   \
     case m:                                                                         \
-        return act_ld ? launch_adj_b<m, true>(dc, dt, blocks, grad_c, act_ld, s)    \
-                      : launch_adj_b<m, false>(dc, dt, blocks, grad_c, 0, s);
+        return act_ld ? launch_adj_b<m, true>(dc, dt, blocks, grad_c, s)            \
+                      : launch_adj_b<m, false>(dc, dt, blocks, grad_c, s);
         WSKP_M(1) WSKP_M(2) WSKP_M(3) WSKP_M(4) WSKP_M(5) WSKP_M(6) WSKP_M(7) WSKP_M(8)
 #undef WSKP_M
     default: return hipErrorInvalidValue;

@@ -592,7 +592,7 @@ def mode_kernels(args):
     c0 = c[0].contiguous()
     t_mr = timed(lambda: wskp.mr_reconstruct(dn2.h, heads, c0, alphas, mod[0].contiguous()))
     mr = {"workload": f"{W}x{H}, 3 levels, kernels (3, 5) per level", "us": t_mr,
-          "launches": "2 pools + 3 decodes + 2 blends"}
+          "launches": "1 filtering of every level (pooling as it stages) + 1 blend"}
     log(f"[kernels] multi-resolution reconstruction {t_mr:.1f} us")
     dn.close()
     dn2.close()

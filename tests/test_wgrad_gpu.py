@@ -150,6 +150,24 @@ def test_large_batches_against_oracle(cfg, sizes):
     dn.close()
 
 
+def test_input_gradients_of_more_than_256_channels():
+    """A decoder of 448 input channels.  Small weights and biases of one keep every
+    pre-activation away from the ReLU's zero, on whose other side the rounding of a
+    forward pass may put one of so few pixels."""
+    cfg = synth.NetConfig(levels=2, channels=(192, 256), kernel_sizes=(3,))
+    parts = []
+    rng = np.random.default_rng(8)
+    for name, ci, co in synth.conv_shapes(cfg):
+        parts += [(0.05 * np.sqrt(2.0 / (9 * ci)) * rng.standard_normal(co * ci * 9)).astype(np.float32),
+                  np.full(co, 0.0 if name == "head" else 1.0, np.float32)]
+    g, ref = _grads(cfg, np.concatenate(parts), synth.make_frame(80, 24, 40))
+    off = 0
+    for name, ci, co in synth.conv_shapes(cfg):
+        n = ci * co * 9 + co
+        assert rel_l2(g[off:off + n], ref[off:off + n]) <= TOL_GRAD, name
+        off += n
+
+
 def test_split_weights_follow_an_adam_step():
     """A frame of the split kernel after a step equals, bit for bit, that of a new handle
     with the weights read back."""
